@@ -212,14 +212,18 @@ size_t calib_stats_bytes(int H, int T) {
     return ((size_t)H * nt * nt * 2 * sizeof(double) + 255) & ~(size_t)255;
 }
 size_t calib_workspace_bytes(int H, int T) {
-    const size_t nr = (size_t)((T + saf::CAL_FIN_ROWS - 1) / saf::CAL_FIN_ROWS);
-    const size_t nc = (size_t)((T + saf::CAL_FIN_COLS - 1) / saf::CAL_FIN_COLS);
+    const size_t nr = (size_t)((T + saf::TRI_ROWS - 1) / saf::TRI_ROWS);
+    const size_t nc = (size_t)((T + saf::TRI_COLS - 1) / saf::TRI_COLS);
     return ((size_t)H * nr * nc * sizeof(double) + 255) & ~(size_t)255;
 }
 
 template <typename T>
 saf_status_t launch_calib_accum(const saf::CalibArgs& args, hipStream_t stream) {
-    const unsigned grid = (unsigned)((size_t)args.H * args.n_tiles * args.n_tiles);
+    // Lower tiles, and on the first call the upper ones, which it zeroes.
+    const int lower = saf::tri_lower(args.n_tiles);
+    const int per = saf::tri_per_xcd(args.H, lower) +
+                    (args.n_seen == 0 ? saf::tri_per_xcd(args.H, lower - args.n_tiles) : 0);
+    const unsigned grid = 8u * (unsigned)per;
     if (args.m2 != nullptr)
         hipLaunchKernelGGL((saf::calib_accum_kernel<T, true>), dim3(grid), dim3(saf::CAL_THREADS), 0, stream, args);
     else
@@ -673,14 +677,13 @@ SAF_EXPORT saf_status_t saf_calib_finalize(int H, int T, int n_total, const floa
     args.T = T;
     args.n_total = n_total;
     args.n_tiles = calib_tiles(T);
-    args.n_cgroups = (T + saf::CAL_FIN_COLS - 1) / saf::CAL_FIN_COLS;
-    args.n_rchunks = (T + saf::CAL_FIN_ROWS - 1) / saf::CAL_FIN_ROWS;
+    args.n_blocks = (T + saf::TRI_ROWS - 1) / saf::TRI_ROWS;
     const size_t n_eta = (size_t)H * T;
     hipLaunchKernelGGL(saf::calib_fill_kernel, dim3(fill_grid(n_eta)), dim3(256), 0, stream, eta_abs, n_eta);
     hipLaunchKernelGGL(saf::calib_fill_kernel, dim3(fill_grid(n_eta)), dim3(256), 0, stream, eta_rel, n_eta);
     if (launched() != SAF_OK) return SAF_ERR_LAUNCH;
-    const unsigned grid = (unsigned)((size_t)H * args.n_rchunks * args.n_cgroups);
-    hipLaunchKernelGGL(saf::calib_final_kernel, dim3(grid), dim3(saf::CAL_FIN_COLS), 0, stream, args);
+    const unsigned grid = 8u * (unsigned)saf::tri_per_xcd(H, saf::tri_lower(args.n_blocks));
+    hipLaunchKernelGGL(saf::calib_final_kernel, dim3(grid), dim3(saf::CAL_FIN_THREADS), 0, stream, args);
     if (launched() != SAF_OK) return SAF_ERR_LAUNCH;
     hipLaunchKernelGGL(saf::calib_scores_kernel, dim3(H), dim3(256), 0, stream, args);
     return launched();
@@ -765,7 +768,7 @@ SAF_EXPORT saf_status_t saf_fit_targets(int H, int T, const float* mean, float f
     hipLaunchKernelGGL(saf::fit_fill_kernel, dim3(fill_grid(ht)), dim3(256), 0, stream, eta_abs, ht);
     hipLaunchKernelGGL(saf::fit_fill_kernel, dim3(fill_grid(ht)), dim3(256), 0, stream, eta_rel, ht);
     hipLaunchKernelGGL(saf::fit_rowsum_kernel, dim3((unsigned)(H * ((T + 3) / 4))), dim3(256), 0, stream, f);
-    const unsigned grid = (unsigned)((size_t)H * f.n_rchunks * f.n_cgroups);
+    const unsigned grid = 8u * (unsigned)saf::tri_per_xcd(H, saf::tri_lower(f.n_rchunks));
     hipLaunchKernelGGL(saf::fit_target_kernel, dim3(grid), dim3(saf::FIT_COLS), 0, stream, f);
     hipLaunchKernelGGL(saf::fit_entropy_kernel, dim3(H), dim3(256), 0, stream, f);
     return launched();

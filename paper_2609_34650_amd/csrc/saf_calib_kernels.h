@@ -27,7 +27,11 @@
 // loads straight to LDS) while this one is used.  Tiles above the diagonal
 // hold zeros (written on the first call only); diagonal tiles mask keys after
 // the query (a wavefront skips its row blocks that lie wholly above the
-// diagonal), and the last row of tiles masks rows past T.
+// diagonal), and the last row of tiles masks rows past T.  The call is bound by
+// the state it reads and writes once each (831 MB with two inputs of 12 heads
+// at T = 4096: 0.197 ms, 4.2 TB/s; 0.350 ms before the tiles were dealt to the
+// XCDs in runs and the state moved past the caches' other users with
+// non-temporal loads and stores, which alone give 7 %).
 //
 // Each tile's entropy and squared-deviation sums live in a slot of its own in
 // the state (float64), so no two workgroups ever write the same address.
@@ -38,8 +42,8 @@
 // mean * ln(mean).  Block sums of the marginals are added atomically in
 // float32 (at most T/256 adds per address); the block's mean * ln(mean) sum
 // goes to a slot of its own; one workgroup per head then sums the slots.
-// Bound by the read of the triangle: 108 us for 12 heads at T = 4096 (403 MB,
-// 3.7 TB/s; walking columns and diagonals separately took 578 us).
+// Bound by the read of the triangle: 90 us for 12 heads at T = 4096 (403 MB,
+// 4.5 TB/s; walking columns and diagonals separately took 578 us).
 #pragma once
 
 #include "saf_common.h"
@@ -49,8 +53,7 @@ namespace saf {
 
 constexpr int CAL_TILE = 128;     // queries and keys per workgroup tile
 constexpr int CAL_THREADS = 256;
-constexpr int CAL_FIN_COLS = 256;  // columns per finalisation workgroup
-constexpr int CAL_FIN_ROWS = 256;  // rows per finalisation workgroup
+constexpr int CAL_FIN_THREADS = TRI_COLS;
 
 struct CalibArgs {
     const void* q;      // [B, H, T, 64]
@@ -70,8 +73,8 @@ struct CalibFinalArgs {
     float* eta_rel;       // [H, T]
     float* s_var;         // [H]
     float* s_kl;          // [H]
-    double* part;         // [H, n_rchunks, n_cgroups]: sum of mean * ln(mean) per block
-    int H, T, n_total, n_tiles, n_cgroups, n_rchunks;
+    double* part;         // [H, lower blocks]: sum of mean * ln(mean) per block
+    int H, T, n_total, n_tiles, n_blocks;  // n_blocks: 256-row blocks of the finalisation
 };
 
 __global__ void calib_fill_kernel(float* p, size_t n) {
@@ -147,6 +150,27 @@ __device__ __forceinline__ void calib_input(Q0 qa, Q1 qb, K0 ka, K1 kb, LS ls, i
     }
 }
 
+// Tile of a workgroup: every XCD takes a run of consecutive tiles (saf_tri.h),
+// the lower ones first and then, on the first call, the upper ones.  False
+// for a workgroup past the end.
+__device__ __forceinline__ bool calib_tile_of(const CalibArgs& p, int& h, int& I, int& J) {
+    const int lower = tri_lower(p.n_tiles);
+    const int upper = lower - p.n_tiles;
+    const int x = (int)(blockIdx.x & 7);
+    int k = (int)(blockIdx.x >> 3);
+    const int per = tri_per_xcd(p.H, lower);
+    const bool low = k < per;
+    const int tiles = low ? lower : upper;
+    k = low ? x * per + k : x * tri_per_xcd(p.H, upper) + (k - per);
+    if (k >= p.H * tiles) return false;
+    h = k / tiles;
+    int r, c;
+    tri_entry(k - h * tiles, r, c);
+    I = low ? r : c;
+    J = low ? c : r + 1;
+    return true;
+}
+
 template <typename T, bool M2>
 __global__ __launch_bounds__(CAL_THREADS) __attribute__((amdgpu_waves_per_eu(M2 ? 2 : 3))) void calib_accum_kernel(
     CalibArgs p) {
@@ -162,11 +186,8 @@ __global__ __launch_bounds__(CAL_THREADS) __attribute__((amdgpu_waves_per_eu(M2 
     __shared__ __attribute__((aligned(16))) float ls1[CAL_TILE];
     __shared__ float red[8];
 
-    const int nt2 = p.n_tiles * p.n_tiles;
-    const int h = (int)(blockIdx.x / nt2);
-    const int tile = (int)(blockIdx.x % nt2);
-    const int I = tile / p.n_tiles;
-    const int J = tile % p.n_tiles;
+    int h, I, J;
+    if (!calib_tile_of(p, h, I, J)) return;
     const int tid = threadIdx.x;
     CalLane L;
     L.w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -204,12 +225,12 @@ __global__ __launch_bounds__(CAL_THREADS) __attribute__((amdgpu_waves_per_eu(M2 
             mean[rb][v] = 0.0f;
             if constexpr (M2) inc[rb][v] = 0.0f;
         }
-    double* slot = p.stats + 2 * (size_t)blockIdx.x;
+    double* slot = p.stats + 2 * ((size_t)(h * p.n_tiles + I) * p.n_tiles + J);
     const bool diag = (I == J);
     const int rows_valid = min(CAL_TILE, L.T - L.row0);
-    if (J > I) {  // above the diagonal: zeros, written once
-        if (p.n_seen == 0 && tid < 2) slot[tid] = 0.0;
-        if (p.n_seen == 0 && col < L.T) {
+    if (J > I) {  // above the diagonal: zeros, written once (the first call's grid alone has these tiles)
+        if (tid < 2) slot[tid] = 0.0;
+        if (col < L.T) {
             const int lo = lane_off();
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb)
@@ -229,7 +250,7 @@ __global__ __launch_bounds__(CAL_THREADS) __attribute__((amdgpu_waves_per_eu(M2 
         for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                if (row_of(rb, v) < L.T) mean[rb][v] = Mg[lo + row_step(rb, v)];
+                if (row_of(rb, v) < L.T) mean[rb][v] = __builtin_nontemporal_load(Mg + lo + row_step(rb, v));
     }
 
     float ent = 0.0f;
@@ -291,7 +312,7 @@ __global__ __launch_bounds__(CAL_THREADS) __attribute__((amdgpu_waves_per_eu(M2 
             for (int v = 0; v < 16; ++v) {
                 if (row_of(rb, v) < L.T) {
                     const int at = lo + row_step(rb, v);
-                    Mg[at] = mean[rb][v];
+                    __builtin_nontemporal_store(mean[rb][v], Mg + at);
                     if constexpr (M2) {
                         M2g[at] = p.n_seen > 0 ? M2g[at] + inc[rb][v] : inc[rb][v];
                         inc_sum += inc[rb][v];
@@ -315,21 +336,14 @@ __global__ __launch_bounds__(CAL_THREADS) __attribute__((amdgpu_waves_per_eu(M2 
     }
 }
 
-__global__ __launch_bounds__(CAL_FIN_COLS) void calib_final_kernel(CalibFinalArgs p) {
-    __shared__ double red[CAL_FIN_COLS / 64];
+__global__ __launch_bounds__(CAL_FIN_THREADS) void calib_final_kernel(CalibFinalArgs p) {
+    __shared__ double red[CAL_FIN_THREADS / 64];
     __shared__ TriShared sh;
-    const int per_head = p.n_rchunks * p.n_cgroups;
-    const int h = (int)(blockIdx.x / per_head);
-    const int rem = (int)(blockIdx.x % per_head);
-    const int i0 = (rem / p.n_cgroups) * CAL_FIN_ROWS;
-    const int j_first = (rem % p.n_cgroups) * CAL_FIN_COLS;
-    if (j_first > i0 + CAL_FIN_ROWS - 1) {  // the whole block lies above the diagonal
-        if (threadIdx.x == 0) p.part[blockIdx.x] = 0.0;
-        return;
-    }
+    int h, k, r, c;
+    if (!tri_block_of(blockIdx.x, p.H, p.n_blocks, h, k, r, c)) return;
     const int T = p.T;
     float mlm = 0.0f;  // sum of m log2(m)
-    tri_block(p.mean + (size_t)h * T * T, T, i0, j_first, sh, p.eta_abs + (size_t)h * T, p.eta_rel + (size_t)h * T,
+    tri_block(p.mean + (size_t)h * T * T, T, r * TRI_ROWS, c * TRI_COLS, sh, p.eta_abs + (size_t)h * T, p.eta_rel + (size_t)h * T,
               [&](float m, int) {
                   // v_log_f32 takes normal numbers (a smaller entry adds less than 1e-36).
                   mlm += m >= 0x1p-126f ? m * __builtin_amdgcn_logf(m) : 0.0f;
@@ -341,8 +355,8 @@ __global__ __launch_bounds__(CAL_FIN_COLS) void calib_final_kernel(CalibFinalArg
     if (threadIdx.x == 0) {
         double t = 0.0;
 #pragma unroll
-        for (int w = 0; w < CAL_FIN_COLS / 64; ++w) t += red[w];
-        p.part[blockIdx.x] = t;
+        for (int w = 0; w < CAL_FIN_THREADS / 64; ++w) t += red[w];
+        p.part[k] = t;
     }
 }
 
@@ -352,7 +366,7 @@ __global__ __launch_bounds__(256) void calib_scores_kernel(CalibFinalArgs p) {
     __shared__ double red[3][4];
     const int h = (int)blockIdx.x;
     const int n_slots = p.n_tiles * p.n_tiles;
-    const int n_parts = p.n_rchunks * p.n_cgroups;
+    const int n_parts = tri_lower(p.n_blocks);
     const double* st = p.stats + 2 * (size_t)h * n_slots;
     const double* pt = p.part + (size_t)h * n_parts;
     double e = 0.0, q = 0.0, m = 0.0;

@@ -8,8 +8,9 @@
 // pass (fit_target_kernel) gives eta_abs (column sums of Pi), eta_rel (its
 // diagonal sums) and sum Pi ln Pi in one read of the triangle (saf_tri.h);
 // block partials of the marginals are added atomically, the entropy partial
-// goes to a slot of its own.  Both are bound by their reads: 181 us together
-// for 12 heads at T = 4096 (2 x 403 MB, 4.5 TB/s; 765 us when the second pass
+// goes to a slot of its own.  Both are bound by their reads: 152 us together
+// for 12 heads at T = 4096 (2 x 403 MB, 5.3 TB/s, part of the second read from
+// the last-level cache; 765 us when the second pass
 // walked columns and diagonals separately and the first read 4 bytes a lane).
 //
 // Fitter: alpha = 0, rho(delta) = log max(eta_rel(delta) / (T - delta),
@@ -41,7 +42,7 @@ struct FitArgs {
     float* rowsum;       // [H, T]: 1 / row sum
     float* eta_abs;      // [H, T]
     float* eta_rel;      // [H, T]
-    double* part;        // [H, n_rchunks * n_cgroups]: per block sum of Pi ln Pi
+    double* part;        // [H, lower blocks]: per block sum of Pi ln Pi
     double* neg_entropy; // [H]
     float* alpha;        // [H, T]
     float* rho;          // [H, T]
@@ -92,24 +93,17 @@ __global__ __launch_bounds__(256) void fit_rowsum_kernel(FitArgs p) {
     if (lane == 0) p.rowsum[(size_t)h * p.T + i] = 1.0f / s;
 }
 
-// Block (head, 256-row chunk, 256-column group); see the header comment.
+// Block (head, 256 rows, 256 columns); see the header comment.
 __global__ __launch_bounds__(FIT_COLS) void fit_target_kernel(FitArgs p) {
     __shared__ double red[FIT_COLS / 64];
     __shared__ TriShared sh;
-    const int per_head = p.n_rchunks * p.n_cgroups;
-    const int h = (int)(blockIdx.x / per_head);
-    const int rem = (int)(blockIdx.x % per_head);
-    const int i0 = (rem / p.n_cgroups) * FIT_ROWS;
-    const int j_first = (rem % p.n_cgroups) * FIT_COLS;
-    if (j_first > i0 + FIT_ROWS - 1) {  // the whole block lies above the diagonal
-        if (threadIdx.x == 0) p.part[blockIdx.x] = 0.0;
-        return;
-    }
+    int h, k, r, c;
+    if (!tri_block_of(blockIdx.x, p.H, p.n_rchunks, h, k, r, c)) return;
     const int T = p.T;
     const float* __restrict__ s = p.rowsum + (size_t)h * T;
     const float fl = p.floor_value;
     float ent = 0.0f;  // sum of Pi log2(Pi)
-    tri_block(p.mean + (size_t)h * T * T, T, i0, j_first, sh, p.eta_abs + (size_t)h * T, p.eta_rel + (size_t)h * T,
+    tri_block(p.mean + (size_t)h * T * T, T, r * TRI_ROWS, c * TRI_COLS, sh, p.eta_abs + (size_t)h * T, p.eta_rel + (size_t)h * T,
               [&](float m, int i) {
                   const float pc = fmaxf(m, fl) * s[i];
                   ent += pc * __builtin_amdgcn_logf(pc);
@@ -122,7 +116,7 @@ __global__ __launch_bounds__(FIT_COLS) void fit_target_kernel(FitArgs p) {
         double t = 0.0;
 #pragma unroll
         for (int w = 0; w < FIT_COLS / 64; ++w) t += red[w];
-        p.part[blockIdx.x] = t;
+        p.part[k] = t;
     }
 }
 
@@ -130,7 +124,7 @@ __global__ __launch_bounds__(FIT_COLS) void fit_target_kernel(FitArgs p) {
 __global__ __launch_bounds__(256) void fit_entropy_kernel(FitArgs p) {
     __shared__ double red[4];
     const int h = (int)blockIdx.x;
-    const int n = p.n_rchunks * p.n_cgroups;
+    const int n = tri_lower(p.n_rchunks);
     double t = 0.0;
     for (int k = (int)threadIdx.x; k < n; k += 256) t += p.part[(size_t)h * n + k];
     t = fit_wave_sum(t);

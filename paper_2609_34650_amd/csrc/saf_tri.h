@@ -17,6 +17,35 @@
 
 namespace saf {
 
+// Row r and column c of entry k of a lower triangle counted row by row (row r
+// starts at r (r + 1) / 2).
+__device__ __forceinline__ void tri_entry(int k, int& r, int& c) {
+    r = (int)((sqrtf(8.0f * (float)k + 1.0f) - 1.0f) * 0.5f);
+    while (r * (r + 1) / 2 > k) --r;
+    while ((r + 1) * (r + 2) / 2 <= k) ++r;
+    c = k - r * (r + 1) / 2;
+}
+
+// Blocks of a triangle of n x n blocks for each of H heads, spread over the 8
+// XCDs (to which workgroups are dealt in turn): each XCD takes a run of
+// consecutive blocks, row by row, so the blocks it has in flight cover whole
+// rows.  Dealing the blocks themselves in turn gives an XCD every eighth piece
+// of a row, and where T is a multiple of 1024 these pieces meet a part of its
+// L2 channels only (calibration call at T = 4096, 512-byte pieces: 0.350 ms so,
+// 0.203 ms in runs).
+__host__ __device__ inline int tri_per_xcd(int H, int blocks) { return (H * blocks + 7) / 8; }
+__host__ __device__ inline int tri_lower(int n) { return n * (n + 1) / 2; }
+
+// Block of workgroup blk in a grid of 8 tri_per_xcd(H, tri_lower(n)); false past the end.
+__device__ __forceinline__ bool tri_block_of(unsigned blk, int H, int n, int& h, int& k, int& r, int& c) {
+    const int lower = tri_lower(n);
+    k = (int)(blk & 7) * tri_per_xcd(H, lower) + (int)(blk >> 3);
+    if (k >= H * lower) return false;
+    h = k / lower;
+    tri_entry(k - h * lower, r, c);
+    return true;
+}
+
 constexpr int TRI_COLS = 256;
 constexpr int TRI_ROWS = 256;
 constexpr int TRI_WROWS = TRI_ROWS / 4;  // rows of a wavefront
