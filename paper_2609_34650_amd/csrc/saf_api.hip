@@ -699,8 +699,8 @@ struct FitLayout {
 };
 FitLayout fit_layout(int H, int T) {
     const size_t ht = (size_t)H * T;
-    const size_t nr = (size_t)((T + saf::FIT_ROWS - 1) / saf::FIT_ROWS);
-    const size_t nc = (size_t)((T + saf::FIT_COLS - 1) / saf::FIT_COLS);
+    const size_t nr = (size_t)((T + saf::TRI_ROWS - 1) / saf::TRI_ROWS);
+    const size_t nc = nr;
     FitLayout l;
     size_t off = 0;
     l.rowsum = off; off += align256(ht * 4);
@@ -727,9 +727,18 @@ saf::FitArgs fit_args(int H, int T, void* workspace) {
     f.logz = reinterpret_cast<float*>(w + l.logz);
     f.H = H;
     f.T = T;
-    f.n_cgroups = (T + saf::FIT_COLS - 1) / saf::FIT_COLS;
-    f.n_rchunks = (T + saf::FIT_ROWS - 1) / saf::FIT_ROWS;
+    f.n_rchunks = (T + saf::TRI_ROWS - 1) / saf::TRI_ROWS;
+    f.zsum = f.rowsum;
+    f.shifts = reinterpret_cast<float*>(w + l.part);  // 8 bytes per head and 256 entries
+    f.n_blocks = (T + 31) / 32;
+    f.n_btiles = (f.n_blocks + 31) / 32;
     return f;
+}
+
+template <int DCH>
+void launch_fit_sums(const saf::FitArgs& f, unsigned grid, hipStream_t stream) {
+    hipLaunchKernelGGL(saf::fit_norm_kernel<DCH>, dim3(grid), dim3(saf::FIT_THREADS), 0, stream, f);
+    hipLaunchKernelGGL(saf::fit_marginals_kernel<DCH>, dim3(grid), dim3(saf::FIT_THREADS), 0, stream, f);
 }
 
 saf_status_t check_fit_shape(int H, int T) {
@@ -769,7 +778,7 @@ SAF_EXPORT saf_status_t saf_fit_targets(int H, int T, const float* mean, float f
     hipLaunchKernelGGL(saf::fit_fill_kernel, dim3(fill_grid(ht)), dim3(256), 0, stream, eta_rel, ht);
     hipLaunchKernelGGL(saf::fit_rowsum_kernel, dim3((unsigned)(H * ((T + 3) / 4))), dim3(256), 0, stream, f);
     const unsigned grid = 8u * (unsigned)saf::tri_per_xcd(H, saf::tri_lower(f.n_rchunks));
-    hipLaunchKernelGGL(saf::fit_target_kernel, dim3(grid), dim3(saf::FIT_COLS), 0, stream, f);
+    hipLaunchKernelGGL(saf::fit_target_kernel, dim3(grid), dim3(saf::TRI_COLS), 0, stream, f);
     hipLaunchKernelGGL(saf::fit_entropy_kernel, dim3(H), dim3(256), 0, stream, f);
     return launched();
 }
@@ -808,10 +817,23 @@ SAF_EXPORT saf_status_t saf_compact_fit(int H, int T, const float* eta_abs, cons
     na.n_rblocks = (T + saf::NORM_ROWS - 1) / saf::NORM_ROWS;
     na.n_fixed = H;
     for (int h = 0; h < H; ++h) na.heads[h] = (unsigned char)h;
-    const size_t ht = (size_t)H * T;
-    const unsigned elem_grid = fill_grid(ht);
+    const unsigned elem_grid = (unsigned)(H * f.n_rchunks);
     const unsigned lse_grid = (unsigned)((size_t)na.n_rblocks * H);
-    const unsigned marg_grid = (unsigned)((size_t)H * f.n_rchunks * f.n_cgroups);
+    // Block distances per workgroup: few enough to give the chip workgroups
+    // (they hide each other's latency), as many as that allows (each adds 1024
+    // results by atomics).  Microseconds a step with 16 / 8 / 4: 12 heads at
+    // T = 4096 (240 workgroups of 16) 19.4 / 20.6 / 27.7; at 2048 (144 of 8)
+    // 16.8 / 14.2 / 14.6; 5 heads at 777 (20 of 8) 16.2 / 13.4 / 12.1.
+    // per_head covers the normalisers' launch; the marginals' tiles
+    // (n_blocks - 32 c distances) need no more.
+    auto per_head = [&](int dch) {
+        int n = 0;
+        for (int c = 0; c < f.n_btiles; ++c) n += (std::min(32 * c + 32, f.n_blocks) + dch - 1) / dch;
+        return n;
+    };
+    const int dch = H * per_head(16) >= 192 ? 16 : H * per_head(8) >= 96 ? 8 : 4;
+    f.per_head = per_head(dch);
+    const unsigned step_grid = (unsigned)((size_t)H * f.per_head);
     hipLaunchKernelGGL(saf::fit_init_kernel, dim3(elem_grid), dim3(256), 0, stream, f);
     if (launched() != SAF_OK) return SAF_ERR_LAUNCH;
     double p1 = 1.0, p2 = 1.0;
@@ -820,8 +842,9 @@ SAF_EXPORT saf_status_t saf_compact_fit(int H, int T, const float* eta_abs, cons
         p2 *= (double)saf::FIT_ADAM_BETA2;
         f.bc1 = (float)(1.0 - p1);
         f.bc2 = (float)(1.0 - p2);
-        hipLaunchKernelGGL(saf::fixed_lse_kernel, dim3(lse_grid), dim3(saf::NORM_THREADS), 0, stream, na);
-        hipLaunchKernelGGL(saf::fit_marginals_kernel, dim3(marg_grid), dim3(saf::FIT_COLS), 0, stream, f);
+        if (dch == 16) launch_fit_sums<16>(f, step_grid, stream);
+        else if (dch == 8) launch_fit_sums<8>(f, step_grid, stream);
+        else launch_fit_sums<4>(f, step_grid, stream);
         hipLaunchKernelGGL(saf::fit_adam_kernel, dim3(elem_grid), dim3(256), 0, stream, f);
         if (launched() != SAF_OK) return SAF_ERR_LAUNCH;
     }

@@ -15,15 +15,13 @@
 //
 // Fitter: alpha = 0, rho(delta) = log max(eta_rel(delta) / (T - delta),
 // floor), then Adam steps on Eq. fit-objective.  One step is three launches
-// for all heads at once: the row normalisers log Z(i) (the forward's
-// fixed_lse_kernel, with one batch element), the marginals of the fitted
-// pattern (fit_marginals_kernel: column and diagonal sums of
-// P(i, j) = exp(alpha(j) + rho(i - j) - log Z(i)), the same walk as above,
-// one exponential per visited entry), and the update (fit_adam_kernel: the
-// gradient (marginal - eta) / T, Adam's moments and step; it also clears the
-// marginal sums for the next step).  fit_kl_kernel forms the acceptance KL,
-// L + (1/T) sum Pi ln Pi with L = (1/T)(sum_i log Z(i) - eta_abs . alpha -
-// eta_rel . rho), in float64.
+// for all heads at once: the row normalisers (fit_norm_kernel), the marginals
+// of the fitted pattern P(i, j) = exp(alpha(j) + rho(i - j) - log Z(i))
+// (fit_marginals_kernel), and the update (fit_adam_kernel: the gradient
+// (marginal - eta) / T, Adam's moments and step; it also clears the sums for
+// the next step).  After the last step the forward's fixed_lse_kernel gives
+// log Z, and fit_kl_kernel the acceptance KL, L + (1/T) sum Pi ln Pi with
+// L = (1/T)(sum_i log Z(i) - eta_abs . alpha - eta_rel . rho), in float64.
 #pragma once
 
 #include "saf_common.h"
@@ -31,8 +29,6 @@
 
 namespace saf {
 
-constexpr int FIT_COLS = 256;  // columns per marginal workgroup
-constexpr int FIT_ROWS = 256;  // rows per marginal workgroup
 constexpr float FIT_ADAM_BETA1 = 0.9f;
 constexpr float FIT_ADAM_BETA2 = 0.999f;
 constexpr float FIT_ADAM_EPS = 1e-8f;
@@ -53,7 +49,11 @@ struct FitArgs {
     float* logz;         // [H, T]
     float* kl;           // [H]
     float floor_value, lr, bc1, bc2;  // bias corrections 1 - beta^t of this step
-    int H, T, n_cgroups, n_rchunks;
+    int H, T, n_rchunks;  // n_rchunks: 256-row blocks of the targets
+    // Fit loop (the targets leave rowsum and part to it):
+    float* zsum;         // [H, T]: Z(i) exp(-A - R) of the step
+    float* shifts;       // [H, n_rchunks, 2]: maxima of alpha and rho over each 256 entries
+    int n_blocks, n_btiles, per_head;  // 32-entry blocks, tiles of 32 blocks, workgroups of a head
 };
 
 __device__ __forceinline__ float fit_wave_sum(float x) {
@@ -94,8 +94,8 @@ __global__ __launch_bounds__(256) void fit_rowsum_kernel(FitArgs p) {
 }
 
 // Block (head, 256 rows, 256 columns); see the header comment.
-__global__ __launch_bounds__(FIT_COLS) void fit_target_kernel(FitArgs p) {
-    __shared__ double red[FIT_COLS / 64];
+__global__ __launch_bounds__(TRI_COLS) void fit_target_kernel(FitArgs p) {
+    __shared__ double red[TRI_COLS / 64];
     __shared__ TriShared sh;
     int h, k, r, c;
     if (!tri_block_of(blockIdx.x, p.H, p.n_rchunks, h, k, r, c)) return;
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(FIT_COLS) void fit_target_kernel(FitArgs p) {
     if (threadIdx.x == 0) {
         double t = 0.0;
 #pragma unroll
-        for (int w = 0; w < FIT_COLS / 64; ++w) t += red[w];
+        for (int w = 0; w < TRI_COLS / 64; ++w) t += red[w];
         p.part[k] = t;
     }
 }
@@ -133,183 +133,351 @@ __global__ __launch_bounds__(256) void fit_entropy_kernel(FitArgs p) {
     if (threadIdx.x == 0) p.neg_entropy[h] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// alpha = 0, rho = log max(eta_rel / (T - delta), floor); moments and
-// marginal sums cleared.
-__global__ void fit_init_kernel(FitArgs p) {
+// This workgroup's maxima of alpha and rho (256 entries of a head).
+__device__ __forceinline__ void fit_put_shifts(const FitArgs& p, float a, float r, float* red) {
+    a = wave_max(a);
+    r = wave_max(r);
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = a;
+        red[4 + (threadIdx.x >> 6)] = r;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const float* x = red + 4 * threadIdx.x;
+        p.shifts[2 * (size_t)blockIdx.x + threadIdx.x] = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+    }
+}
+
+// alpha = 0, rho = log max(eta_rel / (T - delta), floor); moments and sums
+// cleared.  Workgroup = 256 entries of a head.
+__global__ __launch_bounds__(256) void fit_init_kernel(FitArgs p) {
+    __shared__ float red[8];
     const size_t n = (size_t)p.H * p.T;
-    for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-        const int delta = (int)(k % p.T);
-        p.alpha[k] = 0.0f;
-        p.rho[k] = logf(fmaxf(p.eta_rel[k] / (float)(p.T - delta), p.floor_value));
+    const int h = (int)(blockIdx.x / p.n_rchunks);
+    const int delta = (int)(blockIdx.x % p.n_rchunks) * 256 + (int)threadIdx.x;
+    const size_t k = (size_t)h * p.T + delta;
+    float a = -INFINITY, r = -INFINITY;
+    if (delta < p.T) {
+        a = 0.0f;
+        r = logf(fmaxf(p.eta_rel[k] / (float)(p.T - delta), p.floor_value));
+        p.alpha[k] = a;
+        p.rho[k] = r;
         p.m[k] = 0.0f;
         p.m[n + k] = 0.0f;
         p.v[k] = 0.0f;
         p.v[n + k] = 0.0f;
         p.col[k] = 0.0f;
         p.diag[k] = 0.0f;
+        p.zsum[k] = 0.0f;
+    }
+    fit_put_shifts(p, a, r, red);
+}
+
+// ---------------------------------------------------------------------------
+// One step's normalisers and marginals as products with Toeplitz matrices.
+//
+// With A and R the maxima of alpha and rho over the head, ea = exp(alpha - A),
+// er = exp(rho - R), Z'(i) = Z(i) exp(-A - R) and w = 1 / Z',
+//     Z'(i)  = sum_j er(i - j) ea(j)                    (a causal convolution),
+//     col(j) = ea(j) sum_i er(i - j) w(i),
+//     dia(d) = er(d) sum_i ea(i - d) w(i)               (two correlations).
+// Cut every vector into blocks of 32.  For one block distance D, the terms of
+// a convolution are a 32 x 32 Toeplitz matrix of er (entry er(32 D + row -
+// column), 0 at negative offsets) times the blocks of ea, one column per
+// block: 16 float32 MFMAs (32x32x2) for 32 columns, that is for 1024 results
+// and 32 of their distances, where a lane reads 16 + 16 staged values.  (One
+// multiply-add per entry and lane takes as many vector instructions and LDS
+// reads as entries; the float32 matrix cores do 32 a cycle and SIMD.)  The
+// products and sums are float32, as before; a common shift per head replaces
+// the shift per block, and rows whose Z' lies below 2^-57 (FAST_GUARD) take
+// no part in the products and are added entry by entry instead.
+//
+// Workgroup = (head, 32 columns of blocks, DCH distances), the distances
+// shared out to the wavefronts; their tiles are added in LDS and the sums
+// added to memory by float32 atomics.  Bound by the matrix cores (7680 MFMA
+// cycles a SIMD for the two correlations of 12 heads at T = 4096) and by
+// latency: staging, a few dozen MFMAs a wavefront, the atomics.
+// 12 heads at T = 4096: 6.2 us (normalisers) and 10.6 us (marginals) a step,
+// 19.4 us with the update, against 21 + 24 + 5 us (46.4 us a step) for one
+// multiply-add per entry and lane.
+// ---------------------------------------------------------------------------
+constexpr int FIT_THREADS = 512;
+constexpr int FIT_WAVES = FIT_THREADS / 64;
+constexpr int FIT_SPAN = 1024;                           // results per workgroup: 32 blocks
+// DCH: block distances per workgroup, 16, 8 or 4 (saf_compact_fit's rule).
+template <int DCH> constexpr int fit_nx() { return 32 * DCH + 31; }  // staged offsets 32 D0 - 31 .. 32 (D0 + DCH) - 1
+template <int DCH> constexpr int fit_nb() { return 32 + DCH - 1; }   // staged blocks of the other factor
+constexpr int FIT_BSTRIDE = 36;                          // floats per staged block: conflict-free 16-byte reads by column
+constexpr float FIT_MIN_Z = 0x1p-57f;
+
+// A and R of head h: the largest of its chunks' maxima of alpha and rho, as
+// the last update (or the initialisation) left them.  Every wavefront reads
+// them for itself.
+__device__ __forceinline__ void fit_shifts(const FitArgs& p, int h, float& A, float& R) {
+    A = -INFINITY;
+    R = -INFINITY;
+    for (int x = (int)(threadIdx.x & 63); x < p.n_rchunks; x += 64) {
+        const f32x2 m = *reinterpret_cast<const f32x2*>(p.shifts + 2 * ((size_t)h * p.n_rchunks + x));
+        A = fmaxf(A, m[0]);
+        R = fmaxf(R, m[1]);
+    }
+    A = wave_max(A);
+    R = wave_max(R);
+}
+
+__device__ __forceinline__ float fit_exp(float x, float shift) { return fast_exp2((x - shift) * LOG2E); }
+
+// Entries first .. first + N - 1 of x, N / FIT_THREADS a thread, -inf outside 0 .. T - 1 (loads
+// only: a launch is short, so everything it reads is asked for at once).
+template <int N>
+struct FitLoad {
+    float v[(N + FIT_THREADS - 1) / FIT_THREADS];
+    __device__ __forceinline__ void operator()(const float* x, int first, int T) {
+#pragma unroll
+        for (int u = 0; u < (N + FIT_THREADS - 1) / FIT_THREADS; ++u) {
+            const int k = first + (int)threadIdx.x + FIT_THREADS * u;
+            v[u] = (unsigned)k < (unsigned)T ? x[k] : -INFINITY;
+        }
+    }
+    // put(position, exp(x - shift)) for each entry (0 outside).
+    template <typename Put>
+    __device__ __forceinline__ void put(float shift, Put put) const {
+#pragma unroll
+        for (int u = 0; u < (N + FIT_THREADS - 1) / FIT_THREADS; ++u) {
+            const int k = (int)threadIdx.x + FIT_THREADS * u;
+            if (k < N) put(k, fit_exp(v[u], shift));
+        }
+    }
+};
+
+// This workgroup's head, tile of 32 blocks and first distance; `count` gives
+// a tile's distances.  The tiles with most distances come first.  False for
+// a workgroup past the head's last.
+template <int DCH, typename Count>
+__device__ __forceinline__ bool fit_place(int n_tiles, int per_head, bool ascending, Count count, int& h, int& c,
+                                          int& d0) {
+    h = (int)(blockIdx.x / per_head);
+    int k = (int)(blockIdx.x % per_head);
+    for (int u = 0; u < n_tiles; ++u) {
+        c = ascending ? u : n_tiles - 1 - u;
+        const int n = (count(c) + DCH - 1) / DCH;
+        if (k < n) {
+            d0 = k * DCH;
+            return true;
+        }
+        k -= n;
+    }
+    return false;
+}
+
+// The wavefronts' 32 x 32 tiles in LDS, and their sum at x = 32 * column + row.
+__device__ __forceinline__ void fit_put_tile(float* tiles, const f32x16& acc) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    float* t = tiles + w * (32 * 33) + (lane & 31) * 33;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) t[8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)] = acc[v];
+}
+__device__ __forceinline__ float fit_get_tile(const float* tiles, int x) {
+    const int at = (x >> 5) * 33 + (x & 31);
+    float s = 0.0f;
+#pragma unroll
+    for (int w = 0; w < FIT_WAVES; w += 2) s += tiles[w * (32 * 33) + at] + tiles[(w + 1) * (32 * 33) + at];
+    return s;
+}
+
+// Sixteen consecutive floats of a staged block column.
+__device__ __forceinline__ void fit_block(const float* b, float (&y)[16]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(b + 4 * q);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) y[4 * q + u] = v[u];
     }
 }
 
-// Column and diagonal sums of P(i, j) = exp(alpha(j) + rho(i - j) - log Z(i)).
-// The block's rho and alpha values (offsets and keys i - j for its rows and
-// columns: 511 of each) and its rows' log Z are staged in LDS first, so the
-// walk reads consecutive LDS words across a wavefront.
-//
-// Factorised form (no exponential per entry): with A and R the maxima of
-// alpha and rho over the values the block touches, P(i, j) = ea(j) er(i - j)
-// w(i), ea = exp(alpha - A), er = exp(rho - R), w(i) = exp(A + R - log Z(i)),
-// so column j's sum is ea(j) sum_i er(i - j) w(i) and diagonal d's sum is
-// er(d) sum_i ea(i - d) w(i): two multiply-adds per row, with ea, er and w
-// staged in LDS instead of the raw values (entries at negative positions are
-// 0, which masks i < j).  Every term is at most 1, so ea and er cannot
-// overflow; w can, when a row's log Z lies far below A + R, and a block with
-// such a row (more than FAST_GUARD below) evaluates every entry exactly.
-// In the factorised form each staged array is kept as four copies, copy m
-// shifted by m entries, so that a lane's four consecutive entries (whose
-// alignment is fixed per lane) are one aligned 16-byte read; the copies sit
-// FIT_STAGE floats apart (a stride that keeps those reads free of bank
-// conflicts).  The exact form uses copy 0 only.
-constexpr int FIT_STAGE = 2 * FIT_COLS + 16;
-
-__global__ __launch_bounds__(FIT_COLS) void fit_marginals_kernel(FitArgs p) {
-    __shared__ __attribute__((aligned(16))) float rs[4 * FIT_STAGE];
-    __shared__ __attribute__((aligned(16))) float as[4 * FIT_STAGE];
-    __shared__ __attribute__((aligned(16))) float zs[FIT_ROWS];
-    __shared__ float red[4];
-    const int per_head = p.n_rchunks * p.n_cgroups;
-    const int h = (int)(blockIdx.x / per_head);
-    const int rem = (int)(blockIdx.x % per_head);
-    const int i0 = (rem / p.n_cgroups) * FIT_ROWS;
-    const int j_first = (rem % p.n_cgroups) * FIT_COLS;
-    if (j_first > i0 + FIT_ROWS - 1) return;  // the whole block lies above the diagonal
-    const int T = p.T;
-    const int tid = (int)threadIdx.x;
-    const int j = j_first + tid;
-    const bool col_ok = j < T;
+// Z'(i), added into p.zsum (cleared by the step before).  Contraction slot
+// (t, half k) of a distance stands for column 16 k + t of the block.
+template <int DCH>
+__global__ __launch_bounds__(FIT_THREADS) void fit_norm_kernel(FitArgs p) {
+    constexpr int NX = fit_nx<DCH>(), NB = fit_nb<DCH>();
+    __shared__ float er[NX + 1];
+    __shared__ __attribute__((aligned(16))) float ea[NB * FIT_BSTRIDE];
+    __shared__ float tiles[FIT_WAVES * 32 * 33];
+    int h, c, d0;
+    const int nb = p.n_blocks;
+    auto count = [&](int t) { return min(32 * t + 32, nb); };
+    if (!fit_place<DCH>(p.n_btiles, p.per_head, false, count, h, c, d0)) return;
+    const int T = p.T, tid = (int)threadIdx.x;
     const float* __restrict__ al = p.alpha + (size_t)h * T;
     const float* __restrict__ rh = p.rho + (size_t)h * T;
-    const float* __restrict__ lz = p.logz + (size_t)h * T;
-    // Staged index x holds position base + x, base = i0 - j_first - (FIT_COLS - 1).
-    const int base = i0 - j_first - (FIT_COLS - 1);
-    float rv[2], av[2];
-    bool in[2];
-    float am = col_ok ? al[j] : -INFINITY, rm = col_ok ? rh[j] : -INFINITY;
+    const int b0 = 32 * c - d0 - (DCH - 1);  // first staged block of ea
+    FitLoad<NX> lr;
+    FitLoad<32 * NB> la;
+    lr(rh, 32 * d0 - 31, T);
+    la(al, 32 * b0, T);
+    float A, R;
+    fit_shifts(p, h, A, R);
+    lr.put(R, [&](int x, float v) { er[x] = v; });
+    la.put(A, [&](int x, float v) { ea[(x >> 5) * FIT_BSTRIDE + (x & 31)] = v; });
+    __syncthreads();
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, k = lane >> 5;
+    const int d1 = min(d0 + DCH, count(c));
+    f32x16 acc;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int q = base + tid + FIT_COLS * k;
-        in[k] = q >= 0 && q < T;
-        rv[k] = in[k] ? rh[q] : 0.0f;
-        av[k] = in[k] ? al[q] : 0.0f;
-        if (in[k]) {
-            am = fmaxf(am, av[k]);
-            rm = fmaxf(rm, rv[k]);
-        }
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    for (int d = d0 + w; d < d1; d += FIT_WAVES) {
+        float b[16];
+        fit_block(ea + (col + 32 * c - d - b0) * FIT_BSTRIDE + 16 * k, b);
+        const float* e = er + 32 * (d - d0) + col - 16 * k + 31;  // er(32 d + row - 16 k), row = col here
+#pragma unroll
+        for (int t = 0; t < 16; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(e[-t], b[t], acc, 0, 0, 0);
     }
-    const bool row_ok = i0 + tid < T;
-    const float zv = row_ok ? lz[i0 + tid] : 0.0f;
-    const float A = block_max(am, red);
-    const float R = block_max(rm, red);
-    const bool fast = __syncthreads_and(!row_ok || A + R - zv <= FAST_GUARD);
-    const float aj = col_ok ? al[j] : 0.0f;  // column j's alpha
-    const float rj = col_ok ? rh[j] : 0.0f;  // diagonal j's rho
-    const int off = j_first - j + (FIT_COLS - 1);  // staged index of position i - j is (i - i0) + off
-    const int r_beg = max(0, j - i0);               // rows i >= j
-    float c = 0.0f, d = 0.0f;
-    if (fast) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int x = tid + FIT_COLS * k;
-            const float er = in[k] ? fast_exp2((rv[k] - R) * LOG2E) : 0.0f;
-            const float ea = in[k] ? fast_exp2((av[k] - A) * LOG2E) : 0.0f;
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-                if (x >= m) {
-                    rs[m * FIT_STAGE + x - m] = er;
-                    as[m * FIT_STAGE + x - m] = ea;
-                }
-        }
-        zs[tid] = row_ok ? fast_exp2((A + R - zv) * LOG2E) : 0.0f;
-        __syncthreads();
-        if (!col_ok) return;
-        // Rows from r_beg rounded down to a multiple of 4 (the rows below
-        // r_beg meet staged zeros); rows past T have w = 0.  Entry r + off
-        // of the staged arrays is entry r + off - m of copy m, m = off mod 4.
-        const int m = off & 3;
-        const float* rsm = rs + m * FIT_STAGE + off - m;
-        const float* asm_ = as + m * FIT_STAGE + off - m;
-        float c1 = 0.0f, d1 = 0.0f;
-        for (int r = r_beg & ~3; r < FIT_ROWS; r += 4) {
-            const f32x4 w4 = *reinterpret_cast<const f32x4*>(zs + r);
-            const f32x4 e4 = *reinterpret_cast<const f32x4*>(rsm + r);
-            const f32x4 a4 = *reinterpret_cast<const f32x4*>(asm_ + r);
-            c = fmaf(e4[0], w4[0], c);
-            d = fmaf(a4[0], w4[0], d);
-            c1 = fmaf(e4[1], w4[1], c1);
-            d1 = fmaf(a4[1], w4[1], d1);
-            c = fmaf(e4[2], w4[2], c);
-            d = fmaf(a4[2], w4[2], d);
-            c1 = fmaf(e4[3], w4[3], c1);
-            d1 = fmaf(a4[3], w4[3], d1);
-        }
-        c = (c + c1) * fast_exp2((aj - A) * LOG2E);
-        d = (d + d1) * fast_exp2((rj - R) * LOG2E);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            rs[tid + FIT_COLS * k] = rv[k];
-            as[tid + FIT_COLS * k] = av[k];
-        }
-        zs[tid] = zv;
-        __syncthreads();
-        if (!col_ok) return;
-        const int n_rows = min(FIT_ROWS, T - i0);
-        const float aj2 = aj * LOG2E, rj2 = rj * LOG2E;
-        float c1 = 0.0f, d1 = 0.0f;
-        int r = r_beg;
-        for (; r + 2 <= n_rows; r += 2) {
-            const float z0 = zs[r] * LOG2E, z1 = zs[r + 1] * LOG2E;
-            c += fast_exp2(fmaf(rs[r + off], LOG2E, aj2 - z0));
-            c1 += fast_exp2(fmaf(rs[r + 1 + off], LOG2E, aj2 - z1));
-            d += fast_exp2(fmaf(as[r + off], LOG2E, rj2 - z0));
-            d1 += fast_exp2(fmaf(as[r + 1 + off], LOG2E, rj2 - z1));
-        }
-        if (r < n_rows) {
-            const float z0 = zs[r] * LOG2E;
-            c += fast_exp2(fmaf(rs[r + off], LOG2E, aj2 - z0));
-            d += fast_exp2(fmaf(as[r + off], LOG2E, rj2 - z0));
-        }
-        c += c1;
-        d += d1;
-    }
-    if (r_beg < min(FIT_ROWS, T - i0)) {
-        atomicAdd(p.col + (size_t)h * T + j, c);
-        atomicAdd(p.diag + (size_t)h * T + j, d);
+    fit_put_tile(tiles, acc);
+    __syncthreads();
+    for (int x = tid; x < FIT_SPAN; x += FIT_THREADS) {
+        const int i = FIT_SPAN * c + x;
+        if (i < T) atomicAdd(p.zsum + (size_t)h * T + i, fit_get_tile(tiles, x));
     }
 }
 
-// One Adam step on alpha and rho; clears the marginal sums it read.
-__global__ void fit_adam_kernel(FitArgs p) {
-    const size_t n = (size_t)p.H * p.T;
-    const float invT = 1.0f / (float)p.T;
-    for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-        const float g0 = (p.col[k] - p.eta_abs[k]) * invT;
-        const float g1 = (p.diag[k] - p.eta_rel[k]) * invT;
-        p.col[k] = 0.0f;
-        p.diag[k] = 0.0f;
-        float* th[2] = {p.alpha, p.rho};
-        const float g[2] = {g0, g1};
+// col(j) and dia(d), added into p.col and p.diag (cleared by the step before).
+template <int DCH>
+__global__ __launch_bounds__(FIT_THREADS) void fit_marginals_kernel(FitArgs p) {
+    constexpr int NX = fit_nx<DCH>(), NB = fit_nb<DCH>();
+    __shared__ float er[NX + 1], ea[NX + 1];
+    __shared__ __attribute__((aligned(16))) float ws[NB * FIT_BSTRIDE];
+    __shared__ float tiles[FIT_WAVES * 32 * 33];
+    __shared__ float red[2][FIT_WAVES];
+    int h, c, d0;
+    const int nb = p.n_blocks;
+    auto count = [&](int t) { return nb - 32 * t; };
+    if (!fit_place<DCH>(p.n_btiles, p.per_head, true, count, h, c, d0)) return;
+    const int T = p.T, tid = (int)threadIdx.x;
+    const float* __restrict__ al = p.alpha + (size_t)h * T;
+    const float* __restrict__ rh = p.rho + (size_t)h * T;
+    const float* __restrict__ zs = p.zsum + (size_t)h * T;
+    const int i0 = 32 * (32 * c + d0);  // first staged row of w
+    FitLoad<NX> lr, la;
+    FitLoad<32 * NB> lz;
+    FitLoad<FIT_SPAN> oa, orh;  // alpha and rho of the results
+    lr(rh, 32 * d0 - 31, T);
+    la(al, 32 * d0 - 31, T);
+    lz(zs, i0, T);
+    oa(al, FIT_SPAN * c, T);
+    orh(rh, FIT_SPAN * c, T);
+    float A, R;
+    fit_shifts(p, h, A, R);
+    lr.put(R, [&](int x, float v) { er[x] = v; });
+    la.put(A, [&](int x, float v) { ea[x] = v; });
+    bool low = false;  // a row of this tile that the products leave out
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const size_t at = (size_t)q * n + k;
-            const float mq = FIT_ADAM_BETA1 * p.m[at] + (1.0f - FIT_ADAM_BETA1) * g[q];
-            const float vq = FIT_ADAM_BETA2 * p.v[at] + (1.0f - FIT_ADAM_BETA2) * g[q] * g[q];
-            p.m[at] = mq;
-            p.v[at] = vq;
-            const float mhat = mq / p.bc1;
-            const float vhat = vq / p.bc2;
-            th[q][k] -= p.lr * mhat / (sqrtf(vhat) + FIT_ADAM_EPS);
+    for (int u = 0; u < (32 * NB + FIT_THREADS - 1) / FIT_THREADS; ++u) {
+        const int x = tid + FIT_THREADS * u;
+        const bool row = i0 + x < T;
+        const bool small = row && lz.v[u] < FIT_MIN_Z;
+        if (x < FIT_SPAN) low |= small;
+        if (x < 32 * NB) ws[(x >> 5) * FIT_BSTRIDE + (x & 31)] = row && !small ? 1.0f / lz.v[u] : 0.0f;
+    }
+    const bool any_low = __syncthreads_or(low);
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, k = lane >> 5;
+    const int d1 = min(d0 + DCH, count(c));
+    f32x16 ac, ad;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        ac[v] = 0.0f;
+        ad[v] = 0.0f;
+    }
+    for (int d = d0 + w; d < d1; d += FIT_WAVES) {
+        float b[16];
+        fit_block(ws + (col + d - d0) * FIT_BSTRIDE + 16 * k, b);
+        const int at = 32 * (d - d0) - col + 16 * k + 31;  // offset 32 d + 16 k - row, row = col here
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            ac = __builtin_amdgcn_mfma_f32_32x32x2f32(er[at + t], b[t], ac, 0, 0, 0);
+            ad = __builtin_amdgcn_mfma_f32_32x32x2f32(ea[at + t], b[t], ad, 0, 0, 0);
         }
     }
+    const size_t base = (size_t)h * T;
+    fit_put_tile(tiles, ac);
+    __syncthreads();
+    oa.put(A, [&](int x, float e) {
+        if (FIT_SPAN * c + x < T) atomicAdd(p.col + base + FIT_SPAN * c + x, e * fit_get_tile(tiles, x));
+    });
+    __syncthreads();
+    fit_put_tile(tiles, ad);
+    __syncthreads();
+    orh.put(R, [&](int x, float e) {
+        if (FIT_SPAN * c + x < T) atomicAdd(p.diag + base + FIT_SPAN * c + x, e * fit_get_tile(tiles, x));
+    });
+    if (!any_low || d0 != 0) return;
+    // Rows of this tile whose Z' is too small for the shifted products, entry
+    // by entry: log Z(i) with a running maximum, then exp(alpha + rho - log Z).
+    for (int i = FIT_SPAN * c; i < min(FIT_SPAN * (c + 1), T); ++i) {
+        if (!(zs[i] < FIT_MIN_Z)) continue;
+        float m = -INFINITY;
+        for (int j = tid; j <= i; j += FIT_THREADS) m = fmaxf(m, al[j] + rh[i - j]);
+        m = wave_max(m);
+        if (lane == 0) red[0][w] = m;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < FIT_WAVES; ++u) m = fmaxf(m, red[0][u]);
+        float s = 0.0f;
+        for (int j = tid; j <= i; j += FIT_THREADS) s += fast_exp2((al[j] + rh[i - j] - m) * LOG2E);
+        s = fit_wave_sum(s);
+        if (lane == 0) red[1][w] = s;
+        __syncthreads();
+        s = 0.0f;
+#pragma unroll
+        for (int u = 0; u < FIT_WAVES; ++u) s += red[1][u];
+        const float lz = m + __log2f(s) * LN2;
+        for (int j = tid; j <= i; j += FIT_THREADS) {
+            const float pv = fast_exp2((al[j] + rh[i - j] - lz) * LOG2E);
+            atomicAdd(p.col + base + j, pv);
+            atomicAdd(p.diag + base + i - j, pv);
+        }
+    }
+}
+
+// One Adam step on alpha and rho; clears the sums it read.  Workgroup = 256
+// entries of a head, one per thread, every load issued at once; it leaves its
+// entries' maxima for the next step's shifts.
+__global__ __launch_bounds__(256) void fit_adam_kernel(FitArgs p) {
+    __shared__ float red[8];
+    const size_t n = (size_t)p.H * p.T;
+    const int h = (int)(blockIdx.x / p.n_rchunks);
+    const int j = (int)(blockIdx.x % p.n_rchunks) * 256 + (int)threadIdx.x;
+    const size_t k = (size_t)h * p.T + j;
+    const float invT = 1.0f / (float)p.T;
+    float th[2] = {-INFINITY, -INFINITY};
+    if (j < p.T) {
+        const float g[2] = {(p.col[k] - p.eta_abs[k]) * invT, (p.diag[k] - p.eta_rel[k]) * invT};
+        float m[2], v[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            m[q] = p.m[(size_t)q * n + k];
+            v[q] = p.v[(size_t)q * n + k];
+        }
+        th[0] = p.alpha[k];
+        th[1] = p.rho[k];
+        p.col[k] = 0.0f;
+        p.diag[k] = 0.0f;
+        p.zsum[k] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float mq = FIT_ADAM_BETA1 * m[q] + (1.0f - FIT_ADAM_BETA1) * g[q];
+            const float vq = FIT_ADAM_BETA2 * v[q] + (1.0f - FIT_ADAM_BETA2) * g[q] * g[q];
+            p.m[(size_t)q * n + k] = mq;
+            p.v[(size_t)q * n + k] = vq;
+            const float mhat = mq / p.bc1;
+            const float vhat = vq / p.bc2;
+            th[q] -= p.lr * mhat / (sqrtf(vhat) + FIT_ADAM_EPS);
+        }
+        p.alpha[k] = th[0];
+        p.rho[k] = th[1];
+    }
+    fit_put_shifts(p, th[0], th[1], red);
 }
 
 // kl[h] = (sum_i log Z(i) - eta_abs . alpha - eta_rel . rho + sum Pi ln Pi) / T.
