@@ -43,6 +43,12 @@ constexpr float NEG_BIG = -1.0e30f;
 // row's normaliser stays within this many natural-log units of exp(A + R);
 // beyond it a workgroup falls back to exact per-element exponentials.
 constexpr float FAST_GUARD = 40.0f;
+// A sub-block's probabilities are taken against the running maximum as it
+// stands; the maximum is only raised (and the accumulators rescaled) when a
+// lane's partial sum over the sub-block exceeds this bound, so no
+// probability exceeds it either.  Values up to 2^20 are harmless in float32
+// sums and in bf16 operands (same exponent range).
+constexpr float RESCALE_SUM = 1048576.0f;
 // Shifted copies of a Toeplitz band in LDS: copy s starts s entries later, so
 // eight consecutive entries from any start are one aligned 16-byte read.
 constexpr int BAND_COPIES = 8;

@@ -1,4 +1,6 @@
-// Forward of the hybrid causal-attention layer: one launch for all heads.
+// Forward of the hybrid causal-attention layer: one launch for all heads.  (In
+// float32, and where this kernel's grid would be small, the layer takes the
+// grouped-query kernel of saf_gqa.h instead: 128 queries a workgroup.)
 //
 // Workgroup = (batch b, head h, block of 256 queries); 4 wavefronts, each
 // owning 64 consecutive queries as two 32-query column blocks.  The head's
@@ -52,12 +54,6 @@ constexpr int FWD_BM = 256;  // queries per workgroup
 constexpr int FWD_QW = 64;   // queries per wavefront (two 32-query blocks)
 constexpr int FWD_BN = 64;   // keys per tile
 constexpr int FWD_THREADS = 256;
-// A sub-block's probabilities are taken against the running maximum as it
-// stands; the maximum is only raised (and the accumulators rescaled) when a
-// lane's partial sum over the sub-block exceeds this bound, so no
-// probability exceeds it either.  Values up to 2^20 are harmless in float32
-// sums and in bf16 operands (same exponent range).
-constexpr float RESCALE_SUM = 1048576.0f;
 constexpr int FWD_BAND = FWD_BM + FWD_BN - 1;            // offsets met by one tile
 constexpr int FWD_BAND_STRIDE = (FWD_BAND + 7) / 8 * 8 + 8;  // every copy 16-byte aligned
 static_assert(FWD_THREADS / 64 * FWD_QW == FWD_BM, "wavefronts cover the query block");

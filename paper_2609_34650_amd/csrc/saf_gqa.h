@@ -15,9 +15,13 @@
 // tiles of 64 keys go to column-slab LDS tiles D wide by buffer loads straight
 // to LDS, double-buffered; the tiles that meet the diagonal come first with a
 // per-score causal compare.
-//   Ordinary head: online softmax (running maximum raised when a sub-block
-//   exceeds it, accumulator and sum rescaled), O^T += V^T P^T on MFMA, LSE =
-//   m + ln l.
+//   Ordinary head: online softmax, the running maximum raised (accumulator and
+//   sum rescaled) only when a sub-block exceeds it by far, as in the layer
+//   forward; O^T += V^T P^T on MFMA, LSE = m + ln l.  The product operands come
+//   from LDS at 1 KB per MFMA, all of the LDS bandwidth when the matrix cores
+//   run at full rate, so the vector work beside them matters: finding every
+//   sub-block's maximum took the d = 128 prefill (32 heads over 8, B = 4, 4K)
+//   from 0.56 to 0.60 ms all ordinary, 0.52 to 0.55 ms with 10 heads fixed.
 //   Fixed head, factorised (as in the layer forward): P(i, j) =
 //   ea(j) er(i - j) / Z'(i) with ea = exp(a - A), er = exp(r - R) and A, R
 //   the maxima of a and r over the block's positions.  V tiles come by
@@ -63,6 +67,19 @@ struct GqaLane {
     int tid, w, lane, c, hf, m0, q0, N;
 };
 
+// exp2(s * sl2 - m) and this lane's sum.
+__device__ __forceinline__ float gqa_probs(const f32x16& s, float m_run, float sl2, f32x16& pr) {
+    float t0 = 0.0f, t1 = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+        pr[v] = fast_exp2(fmaf(s[v], sl2, -m_run));
+        pr[v + 1] = fast_exp2(fmaf(s[v + 1], sl2, -m_run));
+        t0 += pr[v];
+        t1 += pr[v + 1];
+    }
+    return t0 + t1;
+}
+
 // One 64-key tile (two 32-key sub-blocks) of an ordinary head.
 template <typename T, int D, bool MASK>
 __device__ __forceinline__ void gqa_ord_tile(const T* kt, const T* vt, int n0, const GqaLane& L,
@@ -79,17 +96,23 @@ __device__ __forceinline__ void gqa_ord_tile(const T* kt, const T* vt, int n0, c
         for (int v = 0; v < 16; ++v) s[v] = 0.0f;
 #pragma unroll
         for (int dc = 0; dc < D / 16; ++dc) mma(s, ld_row<T>(kt, 32 * kb + L.c, 16 * dc + 8 * L.hf), qf[dc]);
-        float mx = -INFINITY;
+        if (MASK) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            if (MASK) {
+            for (int v = 0; v < 16; ++v) {
                 const int kk = k0 + 8 * (v >> 2) + 4 * L.hf + (v & 3);
                 s[v] = kk > qq ? -INFINITY : s[v];
             }
-            mx = vmax(mx, s[v]);
         }
-        mx = pair_max(mx) * sl2;
-        if (mx > m_run) {  // raise the running maximum, rescale (per lane; both halves agree)
+        // Probabilities against the running maximum as it stands; it is raised
+        // (and the accumulator rescaled) only when a partial sum shows that the
+        // sub-block exceeds it by far, as in the layer forward.
+        f32x16 pr;
+        float t = gqa_probs(s, m_run, sl2, pr);
+        if (__any(t > RESCALE_SUM)) {
+            float mx = s[0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v) mx = vmax(mx, s[v]);
+            mx = fmaxf(m_run, pair_max(mx) * sl2);
             const float alpha = fast_exp2(m_run - mx);
             m_run = mx;
             l_run *= alpha;
@@ -97,13 +120,7 @@ __device__ __forceinline__ void gqa_ord_tile(const T* kt, const T* vt, int n0, c
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
-        }
-        f32x16 pr;
-        float t = 0.0f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            pr[v] = fast_exp2(fmaf(s[v], sl2, -m_run));
-            t += pr[v];
+            t = gqa_probs(s, m_run, sl2, pr);
         }
         l_run += t;
         frag pb[2];
