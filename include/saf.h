@@ -107,9 +107,10 @@ saf_status_t saf_hybrid_attn_fwd(saf_dtype_t dt,
  *   LSE  : [B, Hq, N] float32;  head_is_fixed, a, r : per query head (Hq).
  * Limits: d in {64, 96, 128}, Hq <= 64, Hq a multiple of Hkv, one slice
  * N * d * sizeof(dt) < 2^31 bytes.  With Hkv == Hq and d == 64 it computes
- * what saf_hybrid_attn_fwd computes (a separate, simpler kernel: one 32-query
- * block per wavefront; one launch, in which a fixed head's workgroup sums its
- * row normalisers from the weights it forms, as in saf_hybrid_attn_fwd).
+ * what saf_hybrid_attn_fwd computes (one 32-query block per wavefront; one
+ * launch, in which a fixed head's workgroup sums its row normalisers from the
+ * weights it forms); saf_hybrid_attn_fwd itself takes this kernel in float32
+ * and where its own grid would leave the chip half empty.
  * Its backward is saf_hybrid_attn_bwd_gqa.
  */
 saf_status_t saf_hybrid_attn_fwd_gqa(saf_dtype_t dt,

@@ -98,20 +98,54 @@ size_t pattern_workspace_bytes(int B, int H, int N) {
            align256(bh * g.n_kblocks * g.n_chunks * (size_t)g.part_len * 4);
 }
 
-template <typename T>
-saf_status_t launch_fwd(const saf::FwdArgs& args, hipStream_t stream) {
-    // One launch: fixed heads form their own row normalisers.
-    const unsigned grid = (unsigned)((size_t)args.n_qblocks * args.B * args.H);
-    hipLaunchKernelGGL(saf::fwd_kernel<T>, dim3(grid), dim3(saf::FWD_THREADS), 0, stream, args);
-    return launched();
-}
-
 // Heads in order of decreasing work for slice_of: ordinary heads, then fixed.
 void fill_head_order(unsigned char* order, uint64_t fixed_mask, int H) {
     int n = 0;
     for (int pass = 0; pass < 2; ++pass)
         for (int h = 0; h < H; ++h)
             if ((int)((fixed_mask >> h) & 1ull) == pass) order[n++] = (unsigned char)h;
+}
+
+// Key/value heads by decreasing work (an ordinary query head weighs 2, a
+// fixed one 1) for slice_of.
+void fill_kv_order(unsigned char* order, uint64_t mask, int Hq, int Hkv) {
+    const int group = Hq / Hkv;
+    int work[64];
+    for (int g = 0; g < Hkv; ++g) {
+        work[g] = 0;
+        for (int i = 0; i < group; ++i) work[g] += ((mask >> (g * group + i)) & 1ull) ? 1 : 2;
+        order[g] = (unsigned char)g;
+    }
+    std::stable_sort(order, order + Hkv, [&](unsigned char x, unsigned char y) { return work[x] > work[y]; });
+}
+
+saf::GqaArgs make_gqa_args(const void* Q, const void* K, const void* V, const float* a, const float* r, int ld_prior,
+                           int B, int Hq, int Hkv, int N, void* O, float* LSE, float scale_log2,
+                           uint64_t fixed_mask) {
+    saf::GqaArgs args;
+    args.q = Q;
+    args.k = K;
+    args.v = V;
+    args.a = a;
+    args.r = r;
+    args.o = O;
+    args.lse = LSE;
+    args.fixed_mask = fixed_mask;
+    args.B = B;
+    args.Hq = Hq;
+    args.Hkv = Hkv;
+    args.N = N;
+    args.ld_prior = ld_prior;
+    args.n_qblocks = (N + saf::GQA_BM - 1) / saf::GQA_BM;
+    args.scale_log2 = scale_log2;
+    fill_kv_order(args.kv_order, fixed_mask, Hq, Hkv);
+    return args;
+}
+
+template <typename T, int D>
+void launch_gqa(const saf::GqaArgs& args, hipStream_t stream) {
+    const unsigned grid = (unsigned)((size_t)args.n_qblocks * args.B * args.Hq);
+    hipLaunchKernelGGL((saf::gqa_fwd_kernel<T, D>), dim3(grid), dim3(saf::GQA_THREADS), 0, stream, args);
 }
 
 size_t workspace_bytes(int B, int H, int N) {
@@ -245,6 +279,26 @@ SAF_EXPORT saf_status_t saf_hybrid_attn_fwd(saf_dtype_t dt, const void* Q, const
     if (!aligned16(V) || !aligned16(O) || !aligned16(LSE) || (Q && !aligned16(Q)) || (K && !aligned16(K)))
         return SAF_ERR_ALIGNMENT;
 
+    const float scale_log2 = saf::LOG2E / sqrtf((float)saf::HEAD_DIM);
+    // Two kernels compute the layer: fwd_kernel (256 queries a workgroup, 64 a
+    // wavefront, so each operand read from LDS feeds two products) and the
+    // grouped-query one with a head a group (128 queries, 32 a wavefront).
+    // bf16: the first, unless its grid is smaller than the 512 workgroups the
+    // chip holds, where twice the workgroups, each half as long, win (us, first
+    // / second: 216 workgroups of N = 1531 36.5 / 33.3, 192 of N = 4096 82 / 67,
+    // 384 of N = 8192 164 / 140, 384 of N = 1024 31.1 / 28.7; but 768 of N = 2048
+    // 70 / 75, 1536 of N = 4096 225 / 255).  float32: the second; two float32
+    // query blocks a wavefront do not fit its registers (N = 129: 34 / 17.5,
+    // 24 heads of N = 2048 315 / 187, 96 of N = 2048 550 / 439, 768 of N = 512
+    // 341 / 255).
+    const int n_qblocks = (N + saf::FWD_BM - 1) / saf::FWD_BM;
+    if (dt == SAF_DTYPE_F32 || (size_t)n_qblocks * B * H < 512) {
+        const saf::GqaArgs args =
+            make_gqa_args(Q, K, V, a, r, ld_prior, B, H, H, N, O, LSE, scale_log2, pr.fixed_mask);
+        if (dt == SAF_DTYPE_BF16) launch_gqa<saf::bf16, saf::HEAD_DIM>(args, stream);
+        else launch_gqa<float, saf::HEAD_DIM>(args, stream);
+        return launched();
+    }
     saf::FwdArgs args;
     args.q = Q;
     args.k = K;
@@ -259,20 +313,13 @@ SAF_EXPORT saf_status_t saf_hybrid_attn_fwd(saf_dtype_t dt, const void* Q, const
     args.N = N;
     args.ld_prior = ld_prior;
     fill_head_order(args.head_order, pr.fixed_mask, H);
-    args.n_qblocks = (N + saf::FWD_BM - 1) / saf::FWD_BM;
-    args.scale_log2 = saf::LOG2E / sqrtf((float)saf::HEAD_DIM);
-    return dt == SAF_DTYPE_BF16 ? launch_fwd<saf::bf16>(args, stream) : launch_fwd<float>(args, stream);
+    args.n_qblocks = n_qblocks;
+    args.scale_log2 = scale_log2;
+    // One launch: fixed heads form their own row normalisers.
+    const unsigned grid = (unsigned)((size_t)n_qblocks * B * H);
+    hipLaunchKernelGGL(saf::fwd_kernel<saf::bf16>, dim3(grid), dim3(saf::FWD_THREADS), 0, stream, args);
+    return launched();
 }
-
-namespace {
-
-template <typename T, int D>
-void launch_gqa(const saf::GqaArgs& args, hipStream_t stream) {
-    const unsigned grid = (unsigned)((size_t)args.n_qblocks * args.B * args.Hq);
-    hipLaunchKernelGGL((saf::gqa_fwd_kernel<T, D>), dim3(grid), dim3(saf::GQA_THREADS), 0, stream, args);
-}
-
-}  // namespace
 
 namespace {
 
@@ -306,19 +353,6 @@ saf_status_t check_gqa(saf_dtype_t dt, const uint8_t* head_is_fixed, const float
     if (pr->mask && (a == nullptr || r == nullptr)) return SAF_ERR_MISSING_PRIOR;
     if (pr->mask && ld_prior < N) return SAF_ERR_SHAPE;
     return SAF_OK;
-}
-
-// Key/value heads by decreasing work (an ordinary query head weighs 2, a
-// fixed one 1) for slice_of.
-void fill_kv_order(unsigned char* order, uint64_t mask, int Hq, int Hkv) {
-    const int group = Hq / Hkv;
-    int work[64];
-    for (int g = 0; g < Hkv; ++g) {
-        work[g] = 0;
-        for (int i = 0; i < group; ++i) work[g] += ((mask >> (g * group + i)) & 1ull) ? 1 : 2;
-        order[g] = (unsigned char)g;
-    }
-    std::stable_sort(order, order + Hkv, [&](unsigned char x, unsigned char y) { return work[x] > work[y]; });
 }
 
 size_t gqa_workspace_bytes(int B, int Hq, int N) {
@@ -358,23 +392,8 @@ SAF_EXPORT saf_status_t saf_hybrid_attn_fwd_gqa(saf_dtype_t dt, const void* Q, c
     if (pr.any_ordinary && (Q == nullptr || K == nullptr)) return SAF_ERR_NULL;
     if (!aligned16(V) || !aligned16(O) || !aligned16(LSE) || (Q && !aligned16(Q)) || (K && !aligned16(K)))
         return SAF_ERR_ALIGNMENT;
-    saf::GqaArgs args;
-    args.q = Q;
-    args.k = K;
-    args.v = V;
-    args.a = a;
-    args.r = r;
-    args.o = O;
-    args.lse = LSE;
-    args.fixed_mask = mask;
-    args.B = B;
-    args.Hq = Hq;
-    args.Hkv = Hkv;
-    args.N = N;
-    args.ld_prior = ld_prior;
-    args.n_qblocks = (N + saf::GQA_BM - 1) / saf::GQA_BM;
-    args.scale_log2 = saf::LOG2E / sqrtf((float)d);
-    fill_kv_order(args.kv_order, mask, Hq, Hkv);
+    const saf::GqaArgs args =
+        make_gqa_args(Q, K, V, a, r, ld_prior, B, Hq, Hkv, N, O, LSE, saf::LOG2E / sqrtf((float)d), mask);
     const bool bf = dt == SAF_DTYPE_BF16;
     if (d == 64) bf ? launch_gqa<saf::bf16, 64>(args, stream) : launch_gqa<float, 64>(args, stream);
     else if (d == 96) bf ? launch_gqa<saf::bf16, 96>(args, stream) : launch_gqa<float, 96>(args, stream);
