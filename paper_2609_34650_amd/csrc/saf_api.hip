@@ -145,7 +145,13 @@ saf::GqaArgs make_gqa_args(const void* Q, const void* K, const void* V, const fl
 template <typename T, int D>
 void launch_gqa(const saf::GqaArgs& args, hipStream_t stream) {
     const unsigned grid = (unsigned)((size_t)args.n_qblocks * args.B * args.Hq);
-    hipLaunchKernelGGL((saf::gqa_fwd_kernel<T, D>), dim3(grid), dim3(saf::GQA_THREADS), 0, stream, args);
+    // float32 at d = 64: one workgroup per CU.  Its MFMAs fill a SIMD by
+    // themselves, and a second workgroup beside a long one only delays it; the
+    // short ones then go to the CUs that finish first (24 heads of N = 2048
+    // 181 to 148 us, 96 of N = 512 54 to 45 us).  Asking for LDS nobody uses
+    // does that.
+    const unsigned spare = sizeof(T) == 4 && D == 64 && grid < 512 ? 16384 : 0;
+    hipLaunchKernelGGL((saf::gqa_fwd_kernel<T, D>), dim3(grid), dim3(saf::GQA_THREADS), spare, stream, args);
 }
 
 size_t workspace_bytes(int B, int H, int N) {
@@ -161,14 +167,14 @@ saf_status_t launch_bwd_stage(saf_bwd_stage_t stage, const saf::BwdArgs& base, h
         const unsigned grid = (unsigned)((rows + saf::PRE_ROWS - 1) / saf::PRE_ROWS);
         hipLaunchKernelGGL(saf::bwd_pre_kernel<T>, dim3(grid), dim3(saf::PRE_THREADS), 0, stream, args);
     } else if (stage == SAF_BWD_DKDV) {
-        args.n_blocks = (args.N + saf::KV_BN - 1) / saf::KV_BN;
+        args.n_blocks = (args.N + saf::kv_ord_bn<T>() - 1) / saf::kv_ord_bn<T>();
         const unsigned grid = (unsigned)((size_t)args.n_blocks * args.B * args.H);
         hipLaunchKernelGGL(saf::bwd_kv_kernel<T>, dim3(grid), dim3(saf::KV_THREADS), 0, stream, args);
     } else {
         // SAF_BWD_DQ reads D from the workspace; SAF_BWD_DQ_WITH_D forms it
         // and writes it there for a key-block pass enqueued after it.
         args.dq_writes_dsum = stage == SAF_BWD_DQ_WITH_D ? 1 : 0;
-        args.n_blocks = (args.N + saf::DQ_BM - 1) / saf::DQ_BM;
+        args.n_blocks = (args.N + saf::dq_bm<T>() - 1) / saf::dq_bm<T>();
         const unsigned grid = (unsigned)((size_t)args.n_blocks * args.B * args.H);
         hipLaunchKernelGGL(saf::bwd_dq_kernel<T>, dim3(grid), dim3(saf::DQ_THREADS), 0, stream, args);
     }

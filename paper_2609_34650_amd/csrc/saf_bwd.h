@@ -72,7 +72,8 @@ __global__ __launch_bounds__(PRE_THREADS) void bwd_pre_kernel(BwdArgs p) {
 
 // ---------------------------------------------------------------------------
 // Key-block pass: workgroup = (b, h, 128 keys); 4 wavefronts x 32 keys,
-// streaming steps of two 64-query tiles from the block's first key to N.
+// streaming steps of two 64-query tiles from the block's first key to N
+// (float32, ordinary heads: 64 keys, 16 a wavefront, steps of one tile).
 // KV_KB 32-key sub-blocks per wavefront: with one, a wavefront stays within
 // 256 VGPRs and two of them share a SIMD.
 //
@@ -110,6 +111,19 @@ constexpr int KV_BAND = KV_BM + KV_BN - 1;                 // offsets per tile
 constexpr int KV_BAND_STRIDE = (KV_BAND + 8) / 8 * 8 + 8;  // every copy 16-byte aligned
 static_assert(BAND_COPIES * KV_BAND_STRIDE * 4 <= tile_elems<bf16>() * 2, "float32 band copies fit in a tile");
 static_assert((KV_BM + KV_BAND + 1) * 4 <= tile_elems<bf16>() * 2, "exact-program rows fit in a tile");
+
+// Ordinary heads: 16-key tiles per wavefront, and so keys per workgroup.  In
+// float32 one instead of two, and one query tile a step instead of two: a
+// float32 MFMA takes 16 times as long for its work, so the longest block
+// rather than the chip's rate sets the time of all but large grids (24 heads of
+// N = 2048: 288 ordinary blocks of 128 keys for 256 CUs, the first of twice the
+// average length), and half the LDS and registers let two workgroups share a
+// CU: 302 to 260 us there, 33.7 to 21.6 us at N = 129, 988 to 943 us for 96 heads.
+// (One key tile with two query tiles: 318, 22.3, 1158 us.)  In bf16 the second
+// key tile halves the LDS reads per product.
+template <typename T> __host__ __device__ constexpr int kv_kt() { return sizeof(T) == 2 ? 2 : 1; }
+template <typename T> __host__ __device__ constexpr int kv_qt() { return sizeof(T) == 2 ? 2 : 1; }  // query tiles a step
+template <typename T> __host__ __device__ constexpr int kv_ord_bn() { return 4 * 16 * kv_kt<T>(); }
 
 struct KvLane {
     int tid, w, lane, c, hf, n, g, n0, kw, N;
@@ -151,18 +165,18 @@ __device__ __forceinline__ void kv_store_zero(T* base, const KvLane& L) {
 
 // One query tile: q_tile / g_tile are the Q / dO tiles, rows holds
 // LSE * log2(e) (first KV_BM floats) and -D (next KV_BM).  The products run on
-// 16 x 16 tiles: per 32-query half, S and dP are 2 x 2 tiles (queries x the
-// wavefront's 32 keys), so a lane holds eight query rows (four of each
+// 16 x 16 tiles: per 32-query half, S and dP are 2 x KT tiles (queries x the
+// wavefront's 16 KT keys), so a lane holds eight query rows (four of each
 // 16-query tile) and reads only those rows' LSE and D; the two query tiles of
 // a key column, stacked, are the B operand of dV^T += dO^T P and
 // dK^T += Q^T dS (k-slot t <-> query 16*(t/4) + 4*g + t%4, the order the
 // transposed reads of dO and Q follow).  The row operands and row values are
 // read first; the transposed operands are issued right after the S and dP
 // products, so they arrive while the softmax runs.
-template <typename T, bool MASK>
+template <typename T, bool MASK, int KT = kv_kt<T>()>
 __device__ __forceinline__ void kv_tile(const T* q_tile, const T* g_tile, const float* rows, int mq, const KvLane& L,
-                                        const typename Vec<T>::x8 (&kf)[2][2], const typename Vec<T>::x8 (&vf)[2][2],
-                                        f32x4 (&dv)[4][2], f32x4 (&dk)[4][2], float scale_log2) {
+                                        const typename Vec<T>::x8 (&kf)[KT][2], const typename Vec<T>::x8 (&vf)[KT][2],
+                                        f32x4 (&dv)[4][KT], f32x4 (&dk)[4][KT], float scale_log2) {
     typedef typename Vec<T>::x8 frag;
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
@@ -183,11 +197,11 @@ __device__ __forceinline__ void kv_tile(const T* q_tile, const T* g_tile, const 
             nd4[qt] = *reinterpret_cast<const f32x4*>(rows + KV_BM + 32 * qb + 16 * qt + 4 * L.g);
             l4[qt] = *reinterpret_cast<const f32x4*>(rows + 32 * qb + 16 * qt + 4 * L.g);
         }
-        f32x4 s[2][2], dp[2][2];
+        f32x4 s[2][KT], dp[2][KT];
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt) {
+            for (int kt = 0; kt < KT; ++kt) {
                 s[qt][kt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
                 dp[qt][kt] = nd4[qt];  // dP - D in one go: the accumulator starts at -D of its rows
             }
@@ -196,13 +210,13 @@ __device__ __forceinline__ void kv_tile(const T* q_tile, const T* g_tile, const 
 #pragma unroll
             for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-                for (int kt = 0; kt < 2; ++kt) mma16(s[qt][kt], qa[qt][dc], kf[kt][dc]);
+                for (int kt = 0; kt < KT; ++kt) mma16(s[qt][kt], qa[qt][dc], kf[kt][dc]);
 #pragma unroll
         for (int dc = 0; dc < 2; ++dc)
 #pragma unroll
             for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-                for (int kt = 0; kt < 2; ++kt) mma16(dp[qt][kt], ga[qt][dc], vf[kt][dc]);
+                for (int kt = 0; kt < KT; ++kt) mma16(dp[qt][kt], ga[qt][dc], vf[kt][dc]);
         // The transposed operands of dV and dK, in flight during the softmax.
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) {
@@ -213,7 +227,7 @@ __device__ __forceinline__ void kv_tile(const T* q_tile, const T* g_tile, const 
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt)
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
+            for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     float pv = fast_exp2(fmaf(s[qt][kt][u], scale_log2, -l4[qt][u]));
@@ -225,7 +239,7 @@ __device__ __forceinline__ void kv_tile(const T* q_tile, const T* g_tile, const 
                     dp[qt][kt][u] = pv * dp[qt][kt][u];
                 }
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
+        for (int kt = 0; kt < KT; ++kt) {
             const frag pb = to_operand16<T>(s[0][kt], s[1][kt]);
             const frag sb = to_operand16<T>(dp[0][kt], dp[1][kt]);
 #pragma unroll
@@ -237,10 +251,10 @@ __device__ __forceinline__ void kv_tile(const T* q_tile, const T* g_tile, const 
     }
 }
 
-// dV or dK rows of the wavefront's 32 keys from 16 x 16 accumulators
+// dV or dK rows of the wavefront's keys from 16 x 16 accumulators
 // (acc[dt][kt]: head dimensions 16 dt .., keys 16 kt ..), times `scale`.
-template <typename T>
-__device__ __forceinline__ void kv_store_rows16(T* base, const KvLane& L, const f32x4 (&acc)[4][2], float scale) {
+template <typename T, int KT = kv_kt<T>()>
+__device__ __forceinline__ void kv_store_rows16(T* base, const KvLane& L, const f32x4 (&acc)[4][KT], float scale) {
     // The lane's key column, recomputed here from the lane index (an
     // instruction pair the compiler cannot merge with the prologue's):
     // otherwise it keeps the K / V row offsets of the prologue, or the
@@ -250,7 +264,7 @@ __device__ __forceinline__ void kv_store_rows16(T* base, const KvLane& L, const 
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
     const int n = lane & 15;
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
+    for (int kt = 0; kt < KT; ++kt) {
         const int key = L.kw + 16 * kt + n;
         if (key >= L.N) continue;
         T* row = base + (size_t)key * HEAD_DIM;
@@ -265,7 +279,7 @@ template <typename T>
 __device__ __forceinline__ void kv_ordinary(const Tiles<T>& sm, const BwdArgs& p, const KvLane& L, size_t base,
                                             size_t row_base) {
     // Tiles of a step's first 64 queries: Q in t[0] / t[1], dO in t[2] / t[3];
-    // of its second 64: Q in t[4] / t[5], dO in t[6] / t[7]; LSE and -D rows of
+    // of its second 64 (bf16): Q in t[4] / t[5], dO in t[6] / t[7]; LSE and -D rows of
     // both in aux[0] / aux[1] (64 LSE, 64 -D, then the same for the second).
     const T* __restrict__ K = reinterpret_cast<const T*>(p.k) + base;
     const T* __restrict__ V = reinterpret_cast<const T*>(p.v) + base;
@@ -273,13 +287,13 @@ __device__ __forceinline__ void kv_ordinary(const Tiles<T>& sm, const BwdArgs& p
     const __amdgpu_buffer_rsrc_t rg = slice_rsrc<T>(reinterpret_cast<const T*>(p.dO) + base, L.N);
     const float* __restrict__ LSE = p.lse + row_base;
     const float* __restrict__ Dsum = p.dsum + row_base;
-    static_assert(KV_KB == 1, "the ordinary program's tiles cover 32 keys per wavefront");
+    constexpr int KT = kv_kt<T>();
     typedef typename Vec<T>::x8 frag;
     // B operands of S and dP: key 16 kt + n of the wavefront, head dimensions
     // 32 dc + 8 g .. 32 dc + 8 g + 7.
-    frag kf[2][2], vf[2][2];
+    frag kf[KT][2], vf[KT][2];
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
+    for (int kt = 0; kt < KT; ++kt) {
         const int key = L.kw + 16 * kt + L.n;
 #pragma unroll
         for (int dc = 0; dc < 2; ++dc) {
@@ -287,19 +301,21 @@ __device__ __forceinline__ void kv_ordinary(const Tiles<T>& sm, const BwdArgs& p
             vf[kt][dc] = key < L.N ? ld8<T>(V + (size_t)key * HEAD_DIM + 32 * dc + 8 * L.g) : zero8<T>();
         }
     }
-    f32x4 dv[4][2], dk[4][2];
+    f32x4 dv[4][KT], dk[4][KT];
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
+        for (int kt = 0; kt < KT; ++kt) {
             dv[dt][kt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             dk[dt][kt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         }
 
-    // Steps of two 64-query tiles (one barrier per 128 queries): the step
+    // Steps of QT 64-query tiles (bf16: one barrier per 128 queries): the step
     // that meets the diagonal first (masked), then the rest.  Rows past N
     // arrive as zeros with LSE = +inf, so they add nothing.
-    constexpr int SB = 2 * KV_BM;
+    constexpr int QT = kv_qt<T>();
+    constexpr int SB = QT * KV_BM;
+    static_assert(SB >= kv_ord_bn<T>(), "the first step covers the diagonal");
     const int n_steps = (L.N - L.n0 + SB - 1) / SB;
     run_slots(
         2, 2 + n_steps - 1, [&](int i) { return i < 2 ? (i == 0 ? 0 : -1) : i - 1; },
@@ -308,8 +324,10 @@ __device__ __forceinline__ void kv_ordinary(const Tiles<T>& sm, const BwdArgs& p
             const int mq = L.n0 + t * SB;
             tile_load_lds<T>(sm.t[b], rq, mq, L.w, L.lane);
             tile_load_lds<T>(sm.t[2 + b], rg, mq, L.w, L.lane);
-            tile_load_lds<T>(sm.t[4 + b], rq, mq + KV_BM, L.w, L.lane);
-            tile_load_lds<T>(sm.t[6 + b], rg, mq + KV_BM, L.w, L.lane);
+            if constexpr (QT == 2) {
+                tile_load_lds<T>(sm.t[4 + b], rq, mq + KV_BM, L.w, L.lane);
+                tile_load_lds<T>(sm.t[6 + b], rg, mq + KV_BM, L.w, L.lane);
+            }
             if (L.tid < SB) {
                 const int row = mq + L.tid;
                 const bool ok = row < L.N;
@@ -324,9 +342,10 @@ __device__ __forceinline__ void kv_ordinary(const Tiles<T>& sm, const BwdArgs& p
             const int mq = L.n0 + t * SB;
             kv_tile<T, decltype(mask)::value>(sm.t[b], sm.t[2 + b], sm.aux[b], mq, L, kf, vf, dv, dk,
                                               p.scale_log2);
-            if (mq + KV_BM < L.N)
-                kv_tile<T, decltype(mask)::value>(sm.t[4 + b], sm.t[6 + b], sm.aux[b] + 2 * KV_BM, mq + KV_BM, L, kf,
-                                                  vf, dv, dk, p.scale_log2);
+            if constexpr (QT == 2)
+                if (mq + KV_BM < L.N)
+                    kv_tile<T, decltype(mask)::value>(sm.t[4 + b], sm.t[6 + b], sm.aux[b] + 2 * KV_BM, mq + KV_BM, L,
+                                                      kf, vf, dv, dk, p.scale_log2);
         });
     kv_store_rows16<T>(reinterpret_cast<T*>(p.dv) + base, L, dv, 1.0f);
     kv_store_rows16<T>(reinterpret_cast<T*>(p.dk) + base, L, dk, p.scale);
@@ -583,15 +602,15 @@ __device__ __forceinline__ void kv_fixed(const Tiles<T>& sm, const BwdArgs& p, c
 }
 
 template <typename T>
-__global__ __launch_bounds__(KV_THREADS) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 2 : 1))) void bwd_kv_kernel(BwdArgs p) {
+__global__ __launch_bounds__(KV_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void bwd_kv_kernel(BwdArgs p) {
     __shared__ __attribute__((aligned(16))) T t0[tile_elems<T>()];
     __shared__ __attribute__((aligned(16))) T t1[tile_elems<T>()];
     __shared__ __attribute__((aligned(16))) T t2[tile_elems<T>()];
     __shared__ __attribute__((aligned(16))) T t3[tile_elems<T>()];
-    __shared__ __attribute__((aligned(16))) T t4[tile_elems<T>()];
-    __shared__ __attribute__((aligned(16))) T t5[tile_elems<T>()];
-    __shared__ __attribute__((aligned(16))) T t6[tile_elems<T>()];
-    __shared__ __attribute__((aligned(16))) T t7[tile_elems<T>()];
+    __shared__ __attribute__((aligned(16))) T t4[kv_qt<T>() == 2 ? tile_elems<T>() : 4];
+    __shared__ __attribute__((aligned(16))) T t5[kv_qt<T>() == 2 ? tile_elems<T>() : 4];
+    __shared__ __attribute__((aligned(16))) T t6[kv_qt<T>() == 2 ? tile_elems<T>() : 4];
+    __shared__ __attribute__((aligned(16))) T t7[kv_qt<T>() == 2 ? tile_elems<T>() : 4];
     __shared__ __attribute__((aligned(16))) float x0[4 * KV_BM];
     __shared__ __attribute__((aligned(16))) float x1[4 * KV_BM];
     __shared__ float red[4];
@@ -608,10 +627,14 @@ __global__ __launch_bounds__(KV_THREADS) __attribute__((amdgpu_waves_per_eu(size
     L.hf = (L.tid >> 5) & 1;
     L.n = L.tid & 15;
     L.g = (L.tid >> 4) & 3;
-    L.n0 = kblk * KV_BN;
-    L.kw = L.n0 + 32 * KV_KB * L.w;
+    L.n0 = kblk * kv_ord_bn<T>();
+    L.kw = L.n0 + 16 * kv_kt<T>() * L.w;
     L.N = p.N;
     if ((p.fixed_mask >> h) & 1ull) {
+        // Fixed programs take 128 keys in either type.
+        constexpr int PER = KV_BN / kv_ord_bn<T>();
+        if (kblk % PER != 0) return;
+        L.kw = L.n0 + 32 * KV_KB * L.w;
         // Batch elements pair up (b0 = b with its low bit cleared, b0 + 1):
         // one workgroup of the pair, the one whose batch parity matches the
         // key block's, forms the pattern's weights once and applies them to
@@ -620,15 +643,20 @@ __global__ __launch_bounds__(KV_THREADS) __attribute__((amdgpu_waves_per_eu(size
         // (odd B) is served alone.  The forward does not pair: its fixed
         // program forms fewer weights per product, and holding two elements'
         // accumulators costs the whole forward kernel registers.
-        const int b0 = sl.b & ~1;
-        const bool paired = b0 + 1 < p.B;
-        if (paired && (sl.b & 1) != (kblk & 1)) return;
+        // In float32 every element is served alone: the products take so long
+        // that forming the weights does not show.
+        const int b0 = sizeof(T) == 2 ? sl.b & ~1 : sl.b;
+        const bool paired = sizeof(T) == 2 && b0 + 1 < p.B;
+        if (paired && (sl.b & 1) != ((kblk / PER) & 1)) return;
         const size_t base = ((size_t)b0 * p.H + h) * p.N * HEAD_DIM;
         const size_t row_base = ((size_t)b0 * p.H + h) * p.N;
-        if (paired)
-            kv_fixed<T, 2>(sm, p, L, base, row_base, h);
-        else
-            kv_fixed<T, 1>(sm, p, L, base, row_base, h);
+        if constexpr (sizeof(T) == 2) {
+            if (paired) {
+                kv_fixed<T, 2>(sm, p, L, base, row_base, h);
+                return;
+            }
+        }
+        kv_fixed<T, 1>(sm, p, L, base, row_base, h);
     } else {
         kv_ordinary<T>(sm, p, L, (size_t)bh * p.N * HEAD_DIM, (size_t)bh * p.N);
     }
@@ -636,14 +664,18 @@ __global__ __launch_bounds__(KV_THREADS) __attribute__((amdgpu_waves_per_eu(size
 
 // ---------------------------------------------------------------------------
 // Query-block pass (ordinary heads): workgroup = (b, h, 128 queries); 4
-// wavefronts x 32 queries, streaming key tiles of 64 up to the diagonal,
+// wavefronts x 32 queries (64 and 16 in float32), streaming key tiles of 64 up to the diagonal,
 // copied by buffer loads straight into double-buffered column-slab LDS tiles.
 // S^T (keys x queries) puts one query per lane, so LSE and D are per-lane
 // scalars and dS^T feeds the B operand of dQ^T += K^T dS^T (K^T through
 // transposing LDS reads).  Tiles below the block's first query run a
 // mask-free body.  Workgroups of fixed heads only write zeros.
 // ---------------------------------------------------------------------------
-constexpr int DQ_BM = 128;
+// Queries per workgroup: 32 a wavefront in bf16, 16 in float32 (see kv_kt; 24
+// heads of N = 2048 224 us with 32, 177 us with 16; N = 129 20.3 and 16.5 us; 96
+// heads 735 and 636 us).
+template <typename T> __host__ __device__ constexpr int dq_qw() { return sizeof(T) == 2 ? 32 : 16; }
+template <typename T> __host__ __device__ constexpr int dq_bm() { return 4 * dq_qw<T>(); }
 constexpr int DQ_BN = TILE_ROWS;
 constexpr int DQ_THREADS = 256;
 
@@ -696,8 +728,47 @@ __device__ __forceinline__ void dq_tile(const T* kt, const T* vt, int n0, const 
     }
 }
 
+// The same on 16 x 16 tiles, 16 queries per wavefront (float32): lane (n, g)
+// holds query n and keys 4 g .. 4 g + 3 of each 16-key tile of S^T and dP^T;
+// two stacked tiles are the B operand of dQ^T += K^T dS^T.
+template <typename T, bool MASK>
+__device__ __forceinline__ void dq_tile16(const T* kt, const T* vt, int n0, const DqLane& L,
+                                          const typename Vec<T>::x8 (&qf)[2], const typename Vec<T>::x8 (&gf)[2],
+                                          float lse2, float dsum, f32x4 (&dq)[4], float scale_log2) {
+    const int n = L.lane & 15, g = L.lane >> 4;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+        const int k0 = n0 + 32 * kb;
+        if (MASK && !(k0 < L.q0 + 16 && k0 < L.N)) continue;  // keys wholly after this wavefront's queries
+        f32x4 s[2], dp[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            s[x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            dp[x] = f32x4{-dsum, -dsum, -dsum, -dsum};
+        }
+#pragma unroll
+        for (int dc = 0; dc < 2; ++dc)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                mma16(s[x], ld_row<T>(kt, 32 * kb + 16 * x + n, 32 * dc + 8 * g), qf[dc]);
+                mma16(dp[x], ld_row<T>(vt, 32 * kb + 16 * x + n, 32 * dc + 8 * g), gf[dc]);
+            }
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float pv = fast_exp2(fmaf(s[x][u], scale_log2, -lse2));
+                if (MASK && k0 + 16 * x + 4 * g + u > L.qq) pv = 0.0f;
+                s[x][u] = pv * dp[x][u];  // dS^T
+            }
+        const typename Vec<T>::x8 sb = to_operand16<T>(s[0], s[1]);
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) mma16(dq[dt], ld_tile_t16(kt, 32 * kb, 16 * dt), sb);
+    }
+}
+
 template <typename T>
-__global__ __launch_bounds__(DQ_THREADS) __attribute__((amdgpu_waves_per_eu(3))) void bwd_dq_kernel(BwdArgs p) {
+__global__ __launch_bounds__(DQ_THREADS) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 3 : 2))) void bwd_dq_kernel(BwdArgs p) {
     __shared__ __attribute__((aligned(16))) T t0[tile_elems<T>()];
     __shared__ __attribute__((aligned(16))) T t1[tile_elems<T>()];
     __shared__ __attribute__((aligned(16))) T t2[tile_elems<T>()];
@@ -716,13 +787,15 @@ __global__ __launch_bounds__(DQ_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
     L.lane = L.tid & 63;
     L.c = L.tid & 31;
     L.hf = (L.tid >> 5) & 1;
-    L.m0 = qblk * DQ_BM;
-    L.q0 = L.m0 + 32 * L.w;
-    L.qq = L.q0 + L.c;
+    constexpr bool WIDE = dq_qw<T>() == 32;  // 32 x 32 tiles
+    constexpr int BM = dq_bm<T>();
+    L.m0 = qblk * BM;
+    L.q0 = L.m0 + dq_qw<T>() * L.w;
+    L.qq = L.q0 + (WIDE ? L.c : L.lane & 15);
     L.N = N;
 
     if (fixed) {  // the whole workgroup takes this branch
-        for (int id = L.tid; id < DQ_BM * (HEAD_DIM / 8); id += DQ_THREADS) {
+        for (int id = L.tid; id < BM * (HEAD_DIM / 8); id += DQ_THREADS) {
             const int row = L.m0 + id / (HEAD_DIM / 8);
             if (row < N) st8<T>(dQ + (size_t)row * HEAD_DIM + (id % (HEAD_DIM / 8)) * 8, zero8<T>());
         }
@@ -736,11 +809,14 @@ __global__ __launch_bounds__(DQ_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
     const __amdgpu_buffer_rsrc_t rv = slice_rsrc<T>(reinterpret_cast<const T*>(p.v) + base, N);
 
     typedef typename Vec<T>::x8 frag;
-    frag qf[4], gf[4];
+    // Operand dc of this lane's query: head dimensions CD dc + 8 part ...
+    constexpr int CD = WIDE ? 16 : 32, NC = HEAD_DIM / CD;
+    const int part = WIDE ? L.hf : L.lane >> 4;
+    frag qf[NC], gf[NC];
 #pragma unroll
-    for (int dc = 0; dc < 4; ++dc) {
-        qf[dc] = L.qq < N ? ld8<T>(Q + (size_t)L.qq * HEAD_DIM + 16 * dc + 8 * L.hf) : zero8<T>();
-        gf[dc] = L.qq < N ? ld8<T>(dO + (size_t)L.qq * HEAD_DIM + 16 * dc + 8 * L.hf) : zero8<T>();
+    for (int dc = 0; dc < NC; ++dc) {
+        qf[dc] = L.qq < N ? ld8<T>(Q + (size_t)L.qq * HEAD_DIM + CD * dc + 8 * part) : zero8<T>();
+        gf[dc] = L.qq < N ? ld8<T>(dO + (size_t)L.qq * HEAD_DIM + CD * dc + 8 * part) : zero8<T>();
     }
     const float lse2 = L.qq < N ? p.lse[(size_t)bh * N + L.qq] * LOG2E : INFINITY;
     float dsum;
@@ -748,26 +824,27 @@ __global__ __launch_bounds__(DQ_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
         // D_i = sum_c dO * O of this lane's query, from the dO fragments
         // already in registers and O's matching columns.
         const T* __restrict__ Orow = reinterpret_cast<const T*>(p.o) + base + (size_t)L.qq * HEAD_DIM;
-        float part = 0.0f;
+        float x = 0.0f;
         if (L.qq < N) {
 #pragma unroll
-            for (int dc = 0; dc < 4; ++dc) part = dot8(ld8<T>(Orow + 16 * dc + 8 * L.hf), gf[dc], part);
+            for (int dc = 0; dc < NC; ++dc) x = dot8(ld8<T>(Orow + CD * dc + 8 * part), gf[dc], x);
         }
-        dsum = pair_sum(part);
-        if (L.qq < N && L.hf == 0) p.dsum[(size_t)bh * N + L.qq] = dsum;
+        if constexpr (!WIDE) x += __shfl_xor(x, 16);
+        dsum = pair_sum(x);
+        if (L.qq < N && part == 0) p.dsum[(size_t)bh * N + L.qq] = dsum;
     } else {
         dsum = L.qq < N ? p.dsum[(size_t)bh * N + L.qq] : 0.0f;
     }
 
-    f32x16 dq[2];
+    typename std::conditional<WIDE, f32x16, f32x4>::type dq[WIDE ? 2 : 4];
 #pragma unroll
-    for (int db = 0; db < 2; ++db)
+    for (int db = 0; db < (WIDE ? 2 : 4); ++db)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) dq[db][v] = 0.0f;
+        for (int v = 0; v < (WIDE ? 16 : 4); ++v) dq[db][v] = 0.0f;
 
     // Slots: the tiles that meet the diagonal first (masked), then the tiles
     // wholly below the block's first query.
-    const int n_tiles = (min(L.m0 + DQ_BM, N) + DQ_BN - 1) / DQ_BN;
+    const int n_tiles = (min(L.m0 + BM, N) + DQ_BN - 1) / DQ_BN;
     const int n_full = L.m0 / DQ_BN;
     const int n_mask = n_tiles - n_full;
     const int P = (n_mask + 1) & ~1;
@@ -781,18 +858,29 @@ __global__ __launch_bounds__(DQ_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
         },
         [&](auto) {},
         [&](auto buf, int t, auto mask) {
-            dq_tile<T, decltype(mask)::value>(kt[decltype(buf)::value], vt[decltype(buf)::value], t * DQ_BN, L, qf,
-                                              gf, lse2, dsum, dq, p.scale_log2);
+            constexpr int b = decltype(buf)::value;
+            if constexpr (WIDE)
+                dq_tile<T, decltype(mask)::value>(kt[b], vt[b], t * DQ_BN, L, qf, gf, lse2, dsum, dq, p.scale_log2);
+            else
+                dq_tile16<T, decltype(mask)::value>(kt[b], vt[b], t * DQ_BN, L, qf, gf, lse2, dsum, dq,
+                                                    p.scale_log2);
         });
 
     if (L.qq < N) {
         T* row = dQ + (size_t)L.qq * HEAD_DIM;
+        if constexpr (WIDE) {
 #pragma unroll
-        for (int db = 0; db < 2; ++db)
+            for (int db = 0; db < 2; ++db)
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                st4<T>(row + 32 * db + 8 * g + 4 * L.hf, dq[db][4 * g] * p.scale, dq[db][4 * g + 1] * p.scale,
-                       dq[db][4 * g + 2] * p.scale, dq[db][4 * g + 3] * p.scale);
+                for (int g = 0; g < 4; ++g)
+                    st4<T>(row + 32 * db + 8 * g + 4 * L.hf, dq[db][4 * g] * p.scale, dq[db][4 * g + 1] * p.scale,
+                           dq[db][4 * g + 2] * p.scale, dq[db][4 * g + 3] * p.scale);
+        } else {
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+                st4<T>(row + 16 * dt + 4 * part, dq[dt][0] * p.scale, dq[dt][1] * p.scale, dq[dt][2] * p.scale,
+                       dq[dt][3] * p.scale);
+        }
     }
 }
 

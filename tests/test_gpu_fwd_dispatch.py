@@ -4,7 +4,8 @@ between them (bf16: 512 workgroups of 256 queries; float32 always takes the
 the fp64 oracle; scores that grow along the row, so that the running maximum
 is raised again and again; and the grouped-query forward with the same.
 
-Bars as for the layer (gpu_helpers): the kernels differ in summation order only.
+Then the float32 backward at the edges of its blocks.  Bars as for the layer
+(gpu_helpers): the kernels differ in summation order only.
 """
 
 import numpy as np
@@ -63,3 +64,13 @@ def test_gqa_growing_scores_raise_the_maximum(dtype, d):
     oO, oL = orc.layer_forward_gqa(inp["Q"], inp["K"], inp["V"], inp["is_fixed"], inp["a"], inp["r"])
     check_close("O", O.double().cpu().numpy(), oO, dtype)
     check_close("LSE", L.double().cpu().numpy(), oL, dtype)
+
+
+@pytest.mark.parametrize("B,H,N", [(1, 4, 15), (1, 4, 16), (3, 4, 17), (1, 4, 48), (2, 4, 49), (1, 4, 64), (3, 5, 80),
+                                   (1, 4, 112), (2, 8, 321)])
+def test_f32_backward_at_its_tile_edges(B, H, N):
+    """16 queries and 16 keys a wavefront, blocks of 64 (fixed heads 128)."""
+    from paper_2609_34650_amd import inputs
+    announce(f"float32 layer B={B} H={H} N={N}")
+    inp = inputs.make_inputs(B, H, N, 64, [1, H - 1], "f32", stream_id=54)
+    compare_layer(run_gpu(inp, "f32"), inp, "f32")
