@@ -55,11 +55,8 @@ constexpr int FWD_QW = 64;   // queries per wavefront (two 32-query blocks)
 constexpr int FWD_BN = 64;   // keys per tile
 constexpr int FWD_THREADS = 256;
 constexpr int FWD_BAND = FWD_BM + FWD_BN - 1;            // offsets met by one tile
-constexpr int FWD_BAND_STRIDE = (FWD_BAND + 7) / 8 * 8 + 8;  // every copy 16-byte aligned
 static_assert(FWD_THREADS / 64 * FWD_QW == FWD_BM, "wavefronts cover the query block");
-static_assert(BAND_COPIES * FWD_BAND_STRIDE * 2 <= tile_elems<bf16>() * 2, "band copies fit in a tile");
 static_assert((FWD_BN + FWD_BAND) * 4 <= tile_elems<bf16>() * 2, "exact-program a and r fit in a tile");
-static_assert(FWD_BAND <= 2 * FWD_THREADS, "two band entries per thread");
 
 struct FwdArgs {
     const void* q;
@@ -358,77 +355,110 @@ __device__ __forceinline__ void fwd_fixed_exact(const Tiles<T>& sm, const FwdArg
 // Fixed heads, factorised program
 // ---------------------------------------------------------------------------
 
+// The band of er lives in a ring: entry er(-x) at ring position x mod 512 for
+// x = key - query of the block's keys and queries, as four shifted copies, so
+// that eight consecutive entries from any start are two aligned 16-byte reads
+// (copy s holds position y + s at y; eight positions past the end repeat the
+// first ones).  Tiles go from the diagonal down to key 0, so a tile's 319
+// entries are the previous tile's and 64 new ones.
+constexpr int FIX_RING = 512;
+constexpr int FIX_COPIES = 4;
+constexpr int FIX_STRIDE = FIX_RING + 8;
+static_assert(FWD_BAND + FWD_BN <= FIX_RING, "a tile's entries and the next tile's new ones fit in the ring");
+static_assert(FIX_COPIES * FIX_STRIDE * 4 <= tile_elems<bf16>() * 2, "the ring fits in a tile");
+
 // Small per-tile values in registers between their loads (issued a tile
-// ahead) and their LDS stores: a of one key, two band entries.  V tiles come
-// by buffer loads straight to LDS, unscaled.
+// ahead) and their LDS stores: wavefront 0 one new band entry a lane,
+// wavefront 1 the a value of one key.  V tiles come by buffer loads straight
+// to LDS, unscaled.
 struct FixStage {
-    float a;      // a of key n0 + L.tid (L.tid < FWD_BN)
-    float rb[2];  // band entries
+    float x;
 };
 
-// Band entry u of the tile at n0 holds offset (m0 - n0 + FWD_BM - 1) - u.
 __device__ __forceinline__ void fix_load(FixStage& st, const float* arow, const float* rrow, int n0,
                                          const FwdLane& L) {
-    st.a = (L.tid < FWD_BN && n0 + L.tid < L.N) ? arow[n0 + L.tid] : -INFINITY;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int u = L.tid + FWD_THREADS * k;
-        const int delta = L.m0 - n0 + (FWD_BM - 1) - u;
-        st.rb[k] = (u < FWD_BAND && delta >= 0 && delta < L.N) ? rrow[delta] : -INFINITY;
+    st.x = -INFINITY;
+    if (L.w == 0) {
+        const int delta = L.m0 - n0 + (FWD_BM - 1) - L.lane;
+        if (delta >= 0 && delta < L.N) st.x = rrow[delta];
+    } else if (L.w == 1) {
+        if (n0 + L.lane < L.N) st.x = arow[n0 + L.lane];
     }
 }
 
-// eas: ea of the tile's keys; band: copy s of er (float32) at
-// s * FWD_BAND_STRIDE, FIX_BAND_COPIES copies (16-byte reads of float32 need
-// four).
-constexpr int FIX_BAND_COPIES = 4;
-static_assert(FIX_BAND_COPIES * FWD_BAND_STRIDE * 4 <= tile_elems<bf16>() * 2, "float32 band copies fit in a tile");
-
-__device__ __forceinline__ void fix_store(float* eas, float* band, const FixStage& st, const FwdLane& L, float a_sh,
-                                          float r_sh) {
-    if (L.tid < FWD_BN) eas[L.tid] = fast_exp2(fmaf(st.a, LOG2E, -a_sh));  // 0 past N
+// Ring entry of x = key - query.
+__device__ __forceinline__ void fix_put(float* ring, int x, float e) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int u = L.tid + FWD_THREADS * k;
-        if (u < FWD_BAND) {
-            const float e = fast_exp2(fmaf(st.rb[k], LOG2E, -r_sh));
-#pragma unroll
-            for (int s = 0; s < FIX_BAND_COPIES; ++s)
-                if (u >= s) band[s * FWD_BAND_STRIDE + u - s] = e;
-        }
+    for (int s = 0; s < FIX_COPIES; ++s) {
+        const int y = (x - s) & (FIX_RING - 1);
+        ring[s * FIX_STRIDE + y] = e;
+        if (y < 8) ring[s * FIX_STRIDE + FIX_RING + y] = e;
     }
 }
 
-// O^T += V^T (band ea)^T: four 16-key chunks; the weight operand of lane
-// (query column c, half hf) in chunk G is band entries u0 .. u0 + 7 times ea
-// of keys 16G + 8hf .. 16G + 8hf + 7, formed in float32 and rounded once.
-// z[qb] collects this lane's share of the row sum Z'(i) of the float32
-// weights (the other lane half holds the other eight keys of each chunk).
-template <typename T, bool MASK>
-__device__ __forceinline__ void fix_tile(const T* vs, const float* band, const float* eas, int n0, const FwdLane& L,
-                                         f32x16 (&oacc)[2][2], float (&z)[2]) {
+// eas: ea of the tile's keys (0 past N); new band entries (0 at negative
+// offsets, the causal mask).
+__device__ __forceinline__ void fix_store(float* eas, float* ring, const FixStage& st, int n0, const FwdLane& L,
+                                          float a_sh, float r_sh) {
+    if (L.w == 0)
+        fix_put(ring, n0 - L.m0 - (FWD_BM - 1) + L.lane, fast_exp2(fmaf(st.x, LOG2E, -r_sh)));
+    else if (L.w == 1)
+        eas[L.lane] = fast_exp2(fmaf(st.x, LOG2E, -a_sh));
+}
+
+// Eight band entries of this lane from ring position x on.
+__device__ __forceinline__ void fix_read(const float* ring, int x, f32x4 (&b)[2]) {
+    const int u = x & (FIX_RING - 1), s = u & (FIX_COPIES - 1);
+    const float* p = ring + s * FIX_STRIDE + u - s;
+    b[0] = *reinterpret_cast<const f32x4*>(p);
+    b[1] = *reinterpret_cast<const f32x4*>(p + 4);
+}
+
+// Entry n of this lane's row of 16 lanes (folds into the instruction that uses it).
+template <int n>
+__device__ __forceinline__ float row_entry(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + n, 0xf, 0xf, true));
+}
+
+// O^T += V^T (band ea)^T: four 16-key chunks, last first; the weight operand
+// of lane (query column c, half hf) in chunk G of query block qb is eight band
+// entries times ea of keys 16G + 8hf .. 16G + 8hf + 7, formed in float32 and
+// rounded once.  z[qb] collects this lane's share of the row sum Z'(i) of the
+// float32 weights (the other lane half holds the other eight keys).
+//
+// What bounds it is the LDS: a product reads 1 KB of V^T for two MFMAs, and a
+// float32 weight operand would take another 2 KB, its ea as much again.  The
+// entries depend on key - query only, so the operand of (G, qb = 1) is that of
+// (G - 2, qb = 0), also across tiles: each chunk reads one new operand for both
+// query blocks (b[G & 3] is chunk G's for qb 1, b[(G + 2) & 3] its for qb 0; the
+// two that the next tile needs stay in b[0] and b[1]).  ea comes as two values
+// a lane and tile, spread by row broadcasts inside the multiplications.  All
+// 12 heads fixed, B = 8, N = 4096: 153 to 146 us; 3 of 12 at N = 32768 1.50 to
+// 1.48 ms.  (Steps of 128 keys, half the barriers, spill: 186 us.)
+template <int G, typename T, bool MASK>
+__device__ __forceinline__ void fix_chunk(const T* vs, const float* ring, int at, float e, int n0, const FwdLane& L,
+                                          f32x4 (&b)[4][2], f32x16 (&oacc)[2][2], float (&z)[2]) {
     typedef typename Vec<T>::x8 frag;
-#pragma unroll
-    for (int G = 0; G < 4; ++G) {
-        if (MASK && n0 + 16 * G > L.q0 + FWD_QW - 1) continue;  // chunk wholly after this wavefront's queries
+    // The chunk's qb = 1 operand; its qb = 0 operand was read two chunks ago.
+    constexpr int NEW = G & 3, OLD = (G + 2) & 3;
+    f32x4 fresh[2];
+    fix_read(ring, at + 16 * (G - 2), fresh);
+    if (!(MASK && n0 + 16 * G > L.q0 + FWD_QW - 1)) {  // else the chunk lies wholly after this wavefront's queries
         frag vf[2];
 #pragma unroll
         for (int db = 0; db < 2; ++db) vf[db] = ld_tile_t<false>(vs, 16 * G, 32 * db);
-        const f32x4 e0 = *reinterpret_cast<const f32x4*>(eas + 16 * G + 8 * L.hf);
-        const f32x4 e1 = *reinterpret_cast<const f32x4*>(eas + 16 * G + 8 * L.hf + 4);
+        float ev[8];
+        static_for<0, 8>([&](auto I) {
+            constexpr int t = decltype(I)::value;
+            ev[t] = row_entry<8 * (G & 1) + t>(e);
+        });
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
-            if (MASK && n0 + 16 * G > L.q0 + 32 * qb + 31) continue;
-            const int ql = L.q0 - L.m0 + 32 * qb + L.c;  // query within the block
-            const int u0 = (FWD_BM - 1) - ql + 16 * G + 8 * L.hf;
-            const int s = u0 & (FIX_BAND_COPIES - 1);
-            const float* bp = band + s * FWD_BAND_STRIDE + u0 - s;
-            const f32x4 b0 = *reinterpret_cast<const f32x4*>(bp);
-            const f32x4 b1 = *reinterpret_cast<const f32x4*>(bp + 4);
             frag w;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const float x0 = b0[t] * e0[t], x1 = b1[t] * e1[t];
+                const float x0 = (qb ? fresh[0][t] : b[OLD][0][t]) * ev[t];
+                const float x1 = (qb ? fresh[1][t] : b[OLD][1][t]) * ev[4 + t];
                 w[t] = (T)x0;
                 w[4 + t] = (T)x1;
                 z[qb] += x0 + x1;
@@ -437,12 +467,27 @@ __device__ __forceinline__ void fix_tile(const T* vs, const float* band, const f
             for (int db = 0; db < 2; ++db) mma(oacc[qb][db], vf[db], w);
         }
     }
+    b[NEW][0] = fresh[0];
+    b[NEW][1] = fresh[1];
+}
+
+template <typename T, bool MASK>
+__device__ __forceinline__ void fix_tile(const T* vs, const float* ring, const float* eas, int n0, const FwdLane& L,
+                                         f32x4 (&b)[4][2], f32x16 (&oacc)[2][2], float (&z)[2]) {
+    const int n = L.lane & 15;
+    const int at = n0 + 8 * L.hf - L.q0 - L.c;  // key - query of the lane's first entry in chunk 0, query block 0
+    const float* ep = eas + 16 * (n >> 3) + 8 * L.hf + (n & 7);
+    const float e0 = ep[0], e1 = ep[32];
+    fix_chunk<3, T, MASK>(vs, ring, at, e1, n0, L, b, oacc, z);
+    fix_chunk<2, T, MASK>(vs, ring, at, e1, n0, L, b, oacc, z);
+    fix_chunk<1, T, MASK>(vs, ring, at, e0, n0, L, b, oacc, z);
+    fix_chunk<0, T, MASK>(vs, ring, at, e0, n0, L, b, oacc, z);
 }
 
 template <typename T>
 __device__ __forceinline__ void fwd_fixed(const Tiles<T>& sm, const FwdArgs& p, const FwdLane& L, size_t base,
                                           size_t row_base, int h) {
-    // Tiles: V in t[0] / t[1], the float32 band in t[2] / t[3], ea in aux.
+    // Tiles: V in t[0] / t[1], the ring of the float32 band in t[2], ea in aux.
     const T* __restrict__ V = reinterpret_cast<const T*>(p.v) + base;
     const float* __restrict__ arow = p.a + (size_t)h * p.ld_prior;
     const float* __restrict__ rrow = p.r + (size_t)h * p.ld_prior;
@@ -485,20 +530,30 @@ __device__ __forceinline__ void fwd_fixed(const Tiles<T>& sm, const FwdArgs& p, 
     const __amdgpu_buffer_rsrc_t rv = slice_rsrc<T>(V, N);
     float z[2] = {0.0f, 0.0f};
     FixStage st;
+    int staged = 0;  // first key of the tile that st belongs to
+    float* ring = reinterpret_cast<float*>(sm.t[2]);
+    // The first tile's band, and its operands of the two chunks above it.
+    const int top = (n_tiles - 1) * FWD_BN;
+    const int first = top - L.m0 - (FWD_BM - 1);  // key - query of its first entry
+    for (int u = L.tid; u < FWD_BAND; u += FWD_THREADS) {
+        const int delta = -(first + u);
+        fix_put(ring, first + u, (delta >= 0 && delta < N) ? fast_exp2(fmaf(rrow[delta], LOG2E, -r_sh)) : 0.0f);
+    }
+    __syncthreads();
+    f32x4 b[4][2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) fix_read(ring, top + 8 * L.hf - L.q0 - L.c + 16 * (2 + k), b[k]);
     run_slots(
-        P, P + n_full, [&](int i) { return i < P ? (i < n_mask ? n_full + i : -1) : i - P; },
+        P, P + n_full, [&](int i) { return i < P ? (i < n_mask ? n_tiles - 1 - i : -1) : n_full - 1 - (i - P); },
         [&](auto buf, int t) {
-            tile_load_lds<T>(sm.t[decltype(buf)::value], rv, t * FWD_BN, L.w, L.lane);
-            fix_load(st, arow, rrow, t * FWD_BN, L);
+            staged = t * FWD_BN;
+            tile_load_lds<T>(sm.t[decltype(buf)::value], rv, staged, L.w, L.lane);
+            fix_load(st, arow, rrow, staged, L);
         },
-        [&](auto buf) {
-            constexpr int b = decltype(buf)::value;
-            fix_store(sm.aux[b], reinterpret_cast<float*>(sm.t[2 + b]), st, L, a_sh, r_sh);
-        },
+        [&](auto buf) { fix_store(sm.aux[decltype(buf)::value], ring, st, staged, L, a_sh, r_sh); },
         [&](auto buf, int t, auto mask) {
-            constexpr int b = decltype(buf)::value;
-            fix_tile<T, decltype(mask)::value>(sm.t[b], reinterpret_cast<const float*>(sm.t[2 + b]), sm.aux[b],
-                                               t * FWD_BN, L, oacc, z);
+            constexpr int k = decltype(buf)::value;
+            fix_tile<T, decltype(mask)::value>(sm.t[k], ring, sm.aux[k], t * FWD_BN, L, b, oacc, z);
         });
     // O(i) = acc(i) / Z'(i) and log Z(i) = A + R + ln Z'(i), with Z'(i) the
     // sum of the same float32 weights (the guard keeps it above e^-40).
