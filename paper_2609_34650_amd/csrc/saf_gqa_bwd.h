@@ -73,6 +73,11 @@ __device__ __forceinline__ void gkv_tile(const T* qt, const T* gt, const float* 
                                          const typename Vec<T>::x8 (&vf)[D / 16], f32x16 (&dv)[D / 32],
                                          f32x16 (&dk)[D / 32], float scale_log2) {
     typedef typename Vec<T>::x8 frag;
+    // The first transposed operands of dV and dK are read before the softmax arithmetic, which then
+    // covers their latency (float16 and bfloat16, both products in one pass: backward of B2 H16 N8192
+    // with 4 fixed heads, d = 64 840 to 791 us, d = 96 1155 to 1143).  The passes of d = 128 hold one
+    // product each and measured the same either way.
+    constexpr bool EK = sizeof(T) == 2 && PART == GKV_BOTH;
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
         const int qs = mq + 32 * qb;
@@ -93,6 +98,15 @@ __device__ __forceinline__ void gkv_tile(const T* qt, const T* gt, const float* 
 #pragma unroll
             for (int dc = 0; dc < D / 16; ++dc) mma(dp, ld_row<T>(gt, 32 * qb + L.c, 16 * dc + 8 * L.hf), vf[dc]);
         }
+        frag ea[D / 32], eb[D / 32];
+        if constexpr (EK) {
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db) {
+                ea[db] = ld_tile_t<true>(gt, 32 * qb, 32 * db);
+                eb[db] = ld_tile_t<true>(qt, 32 * qb, 32 * db);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             const f32x4 l4 = *reinterpret_cast<const f32x4*>(rows + 32 * qb + 8 * g + 4 * L.hf);
@@ -110,12 +124,14 @@ __device__ __forceinline__ void gkv_tile(const T* qt, const T* gt, const float* 
             if constexpr (PART != GKV_DK) {
                 const frag pb = to_operand<T>(s, 8 * kc);
 #pragma unroll
-                for (int db = 0; db < D / 32; ++db) mma(dv[db], ld_tile_t<true>(gt, 32 * qb + 16 * kc, 32 * db), pb);
+                for (int db = 0; db < D / 32; ++db)
+                    mma(dv[db], EK && kc == 0 ? ea[db] : ld_tile_t<true>(gt, 32 * qb + 16 * kc, 32 * db), pb);
             }
             if constexpr (PART != GKV_DV) {
                 const frag sb = to_operand<T>(dp, 8 * kc);
 #pragma unroll
-                for (int db = 0; db < D / 32; ++db) mma(dk[db], ld_tile_t<true>(qt, 32 * qb + 16 * kc, 32 * db), sb);
+                for (int db = 0; db < D / 32; ++db)
+                    mma(dk[db], EK && kc == 0 ? eb[db] : ld_tile_t<true>(qt, 32 * qb + 16 * kc, 32 * db), sb);
             }
         }
     }
@@ -435,6 +451,18 @@ __device__ __forceinline__ void gdq_tile(const T* kt, const T* vt, int n0, const
             mma(s, ld_row<T>(kt, 32 * kb + L.c, 16 * dc + 8 * L.hf), qf[dc]);
             mma(dp, ld_row<T>(vt, 32 * kb + L.c, 16 * dc + 8 * L.hf), gf[dc]);
         }
+        // K^T operands of dQ, in flight during the softmax (16-bit types: d = 128 B4 H32/8 N4096 673 to
+        // 636 us).  Float32 has no registers for them and reads each where it is used: held early they
+        // cost 2-3 % (d = 128 B2 H8/4 N2048 backward 1719 to 1752 us, d = 96 726 to 745).
+        constexpr bool EK = sizeof(T) == 2;
+        frag kta[2][D / 32];
+        if constexpr (EK) {
+#pragma unroll
+            for (int kc = 0; kc < 2; ++kc)
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db) kta[kc][db] = ld_tile_t<true>(kt, 32 * kb + 16 * kc, 32 * db);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             float pv = fast_exp2(fmaf(s[v], scale_log2, -lse2));
@@ -445,7 +473,8 @@ __device__ __forceinline__ void gdq_tile(const T* kt, const T* vt, int n0, const
         for (int kc = 0; kc < 2; ++kc) {
             const frag sb = to_operand<T>(s, 8 * kc);
 #pragma unroll
-            for (int db = 0; db < D / 32; ++db) mma(dq[db], ld_tile_t<true>(kt, 32 * kb + 16 * kc, 32 * db), sb);
+            for (int db = 0; db < D / 32; ++db)
+                mma(dq[db], EK ? kta[kc][db] : ld_tile_t<true>(kt, 32 * kb + 16 * kc, 32 * db), sb);
         }
     }
 }
