@@ -166,7 +166,7 @@ def _check_act(name: str, t: Optional[torch.Tensor], shape, dtype, device, allow
         if allow_none:
             return
         raise ValueError(f"{name} is required")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     if t.dtype != dtype:
         raise TypeError(f"{name} has dtype {t.dtype}, expected {dtype}")
@@ -198,7 +198,11 @@ def _prior(name: str, t: Optional[torch.Tensor], H: int, N: int, device) -> Tupl
 
 
 def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    """Raw handle of the current stream, without a ``torch.cuda.Stream``
+    object built on each call; a device that has no streams is refused."""
+    if device.type != "cuda":
+        return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _raise(code: int, what: str):
@@ -224,10 +228,12 @@ def saf_hybrid_attn_fwd(Q: Optional[torch.Tensor], K: Optional[torch.Tensor], V:
     _check_act("K", K, V.shape, V.dtype, dev, allow_none=True)
     if O is None:
         O = torch.empty_like(V)
+    else:
+        _check_act("O", O, V.shape, V.dtype, dev)
     if LSE is None:
         LSE = torch.empty((B, H, N), dtype=torch.float32, device=dev)
-    _check_act("O", O, V.shape, V.dtype, dev)
-    _check_act("LSE", LSE, (B, H, N), torch.float32, dev)
+    else:
+        _check_act("LSE", LSE, (B, H, N), torch.float32, dev)
     flags = _flags(head_is_fixed, H)
     pa, lda = _prior("a", a, H, N, dev)
     pr, ldr = _prior("r", r, H, N, dev)
@@ -325,13 +331,14 @@ def _bwd_common(Q, K, V, O, dO, LSE, head_is_fixed, a, r, dQ, dK, dV, workspace)
     _check_act("Q", Q, V.shape, V.dtype, dev, allow_none=True)
     _check_act("K", K, V.shape, V.dtype, dev, allow_none=True)
     _check_act("LSE", LSE, (B, H, N), torch.float32, dev)
+    for name, t in (("dQ", dQ), ("dK", dK), ("dV", dV)):
+        if t is not None:
+            _check_act(name, t, V.shape, V.dtype, dev)
     dQ = torch.empty_like(V) if dQ is None else dQ
     dK = torch.empty_like(V) if dK is None else dK
     dV = torch.empty_like(V) if dV is None else dV
-    for name, t in (("dQ", dQ), ("dK", dK), ("dV", dV)):
-        _check_act(name, t, V.shape, V.dtype, dev)
-    nbytes = saf_hybrid_attn_bwd_workspace_bytes(V.dtype, B, H, N, d)
     if workspace is None:
+        nbytes = saf_hybrid_attn_bwd_workspace_bytes(V.dtype, B, H, N, d)
         workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=dev)
     flags = _flags(head_is_fixed, H)
     pa, lda = _prior("a", a, H, N, dev)
@@ -422,9 +429,9 @@ class HybridAttention(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, Q, K, V, head_is_fixed, a, r):
-        O, LSE = saf_hybrid_attn_fwd(Q, K, V, head_is_fixed, a, r)
-        ctx.save_for_backward(Q, K, V, O, LSE, a, r)
         ctx.flags = _flags(head_is_fixed, V.shape[1])
+        O, LSE = saf_hybrid_attn_fwd(Q, K, V, ctx.flags, a, r)
+        ctx.save_for_backward(Q, K, V, O, LSE, a, r)
         return O
 
     @staticmethod
