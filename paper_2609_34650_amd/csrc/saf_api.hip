@@ -273,6 +273,36 @@ saf_status_t launch_calib_accum(const saf::CalibArgs& args, hipStream_t stream) 
 
 }  // namespace
 
+namespace {
+
+// Whether a bf16 layer forward takes the 128-query kernel.  Where the
+// 256-query grid is small, twice the workgroups, each half as long, win; the
+// less so the more heads are fixed, since the 256-query kernel shares each
+// weight operand between its two query blocks.  us of 12 heads, 256 / 128
+// queries, by workgroups of 256 queries:
+//   no head fixed to a third of them, line at 512 (what the chip holds):
+//     192 of N = 4096 82 / 56, 480 of N = 2048 54 / 51; but 768 68.7 / 70.0,
+//     1536 125 / 142;
+//   more than a third, line at 400: 384 of N = 2048 48.0 / 38.4, of N = 512
+//     20.3 / 18.8; but 480 of N = 512 20.9 / 23.1, of N = 129 13.2 / 15.7;
+//   all, line at 256 (one a CU): 192 of N = 1024 22.5 / 20.5; 384 of N = 8192
+//     132 / 137, of N = 512 16.1 / 19.5; 480 of N = 1024 24.3 / 29.9.
+// With three or five blocks of 128 queries the other kernel's last block is at
+// most half full, which costs it a third or more of its work: up to a third
+// fixed, any grid (3072 of N = 300 78.6 / 73.7, of N = 640 121 / 117; 1536
+// 42.6 / 39.6, 63.7 / 58.9; but all fixed 71 / 78, 97 / 114, and four blocks,
+// N = 512, 118 / 131).
+bool fwd_use_128(int B, int H, int N, uint64_t fixed_mask) {
+    const int fixed = __builtin_popcountll(fixed_mask);
+    const size_t grid = (size_t)((N + saf::FWD_BM - 1) / saf::FWD_BM) * B * H;
+    const int half_blocks = (N + saf::GQA_BM - 1) / saf::GQA_BM;
+    if (fixed == H) return grid < 256;
+    if (3 * fixed > H) return grid < 400;
+    return grid < 512 || half_blocks == 3 || half_blocks == 5;
+}
+
+}  // namespace
+
 SAF_EXPORT saf_status_t saf_hybrid_attn_fwd(saf_dtype_t dt, const void* Q, const void* K, const void* V,
                                             const uint8_t* head_is_fixed, const float* a, const float* r,
                                             int ld_prior, int B, int H, int N, int d, void* O, float* LSE,
@@ -289,16 +319,12 @@ SAF_EXPORT saf_status_t saf_hybrid_attn_fwd(saf_dtype_t dt, const void* Q, const
     // Two kernels compute the layer: fwd_kernel (256 queries a workgroup, 64 a
     // wavefront, so each operand read from LDS feeds two products) and the
     // grouped-query one with a head a group (128 queries, 32 a wavefront).
-    // bf16: the first, unless its grid is smaller than the 512 workgroups the
-    // chip holds, where twice the workgroups, each half as long, win (us, first
-    // / second: 216 workgroups of N = 1531 36.5 / 33.3, 192 of N = 4096 82 / 67,
-    // 384 of N = 8192 164 / 140, 384 of N = 1024 31.1 / 28.7; but 768 of N = 2048
-    // 70 / 75, 1536 of N = 4096 225 / 255).  float32: the second; two float32
-    // query blocks a wavefront do not fit its registers (N = 129: 34 / 17.5,
-    // 24 heads of N = 2048 315 / 187, 96 of N = 2048 550 / 439, 768 of N = 512
-    // 341 / 255).
+    // float32: the second; two float32 query blocks a wavefront do not fit its
+    // registers (N = 129: 34 / 17.5 us first / second, 24 heads of N = 2048
+    // 315 / 187, 96 of N = 2048 550 / 439, 768 of N = 512 341 / 255).
+    // bf16: fwd_use_128.
     const int n_qblocks = (N + saf::FWD_BM - 1) / saf::FWD_BM;
-    if (dt == SAF_DTYPE_F32 || (size_t)n_qblocks * B * H < 512) {
+    if (dt == SAF_DTYPE_F32 || fwd_use_128(B, H, N, pr.fixed_mask)) {
         const saf::GqaArgs args =
             make_gqa_args(Q, K, V, a, r, ld_prior, B, H, H, N, O, LSE, scale_log2, pr.fixed_mask);
         if (dt == SAF_DTYPE_BF16) launch_gqa<saf::bf16, saf::HEAD_DIM>(args, stream);

@@ -74,3 +74,22 @@ def test_f32_backward_at_its_tile_edges(B, H, N):
     announce(f"float32 layer B={B} H={H} N={N}")
     inp = inputs.make_inputs(B, H, N, 64, [1, H - 1], "f32", stream_id=54)
     compare_layer(run_gpu(inp, "f32"), inp, "f32")
+
+
+@pytest.mark.parametrize("B,H,N,n_fixed", [(1, 64, 1024, 64), (1, 63, 1024, 63),     # all fixed: 256 workgroups, 252
+                                           (1, 50, 2048, 17), (1, 49, 2048, 17),     # over a third: 400, 392
+                                           (5, 64, 257, 21), (5, 64, 384, 21),       # to a third, short: 128 queries
+                                           (5, 64, 257, 22), (4, 64, 513, 21), (4, 64, 640, 22)])
+def test_bf16_forward_rule_by_fixed_share(B, H, N, n_fixed):
+    """Both kernels on the lines that depend on the share of fixed heads."""
+    from paper_2609_34650_amd import inputs
+    announce(f"forward dispatch by share B={B} H={H} N={N} fixed={n_fixed}")
+    inp = inputs.make_inputs(B, H, N, 64, list(range(H - n_fixed, H)), "bf16", stream_id=55, backward=False)
+    heads = [(0, 0), (B - 1, H - 1), (B // 2, H - n_fixed)]
+    compare_layer(run_gpu(inp, "bf16", backward=False), inp, "bf16", backward=False, heads=heads)
+
+
+def test_growing_scores_raise_the_maximum_of_256_queries():
+    announce("forward growing scores, 256-query kernel, ragged")
+    inp = _case(3, 64, 700, "bf16", grow=True)
+    compare_layer(run_gpu(inp, "bf16", backward=False), inp, "bf16", backward=False, heads=[(0, 0), (2, 62)])
